@@ -75,3 +75,19 @@ def test_cod_workload_shapes_spot_check(B):
         assert got[s] == len(ref.ids), f"sample {s}"
         for name in ("ids", "labels", "pos", "section", "column"):
             assert np.array_equal(host[name][o:o + got[s]], np.asarray(getattr(ref, name), np.int32)), (s, name)
+
+
+@pytest.mark.parametrize("n_samples,lo,hi", [(4200, 2, 6), (4200, 2, 66), (2050, 2, 40), (1100, 2, 130), (700, 2, 40),
+                                             (300, 1000, 1030), (9, 63, 66)])
+def test_cod_wavefronts_per_sample(B, n_samples, lo, hi):
+    """Batches whose size and longest sample take 1, 2, 4, 8 and 16 wavefronts
+    per sample; lengths around the 64-column mask words, subtasks that keep no
+    column (K = 12 of 2-token samples)."""
+    rng = np.random.default_rng(n_samples)
+    lens = [int(x) for x in rng.integers(lo, hi + 1, size=n_samples)]
+    samples = [rng.integers(0, 1000, size=n).astype(np.int64) for n in lens]
+    if n_samples == 2050:
+        samples[7] = rng.integers(0, 1000, size=700).astype(np.int64)   # longest sample: at least 2 wavefronts
+    say(f"[gpu] cod: {n_samples} samples of {lo}-{hi} tokens, K=12")
+    out_offs, host, got = _run(B, samples, 12, 0.7, 0.2, 999, seed=n_samples)
+    _check(samples, out_offs, host, got, 12, 0.7, 0.2, 999, n_samples)
