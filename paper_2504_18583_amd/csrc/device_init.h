@@ -30,9 +30,11 @@ hipError_t launch_rope_table(float2* tab, int cap, int hd, double theta, const R
 // t_start (may be null): receives the device clock at the kernel's start (the
 // start of the pass).  fuse_cnt (may be null): n_sets fused-launch counter
 // sets (kFuseInts ints each) to zero.  ovf: fp16 range flag (f16_flagged).
+// ids: the rows' token ids of a linear pass (null: the descriptor's).
 hipError_t launch_embed(const uint16_t* E, int n_strips, int d, const FwdDesc* desc, float* x, const float* g,
                         uint16_t* xg, int act_rows, float* ss, int ss_stride, int max_rows,
-                        unsigned long long* t_start, int* fuse_cnt, int n_sets, int* ovf, hipStream_t st);
+                        unsigned long long* t_start, int* fuse_cnt, int n_sets, int* ovf, const int* ids,
+                        hipStream_t st);
 hipError_t launch_gather_u16(const uint16_t* src, const size_t* idx, int n, float* out, hipStream_t st);
 
 }  // namespace pard

@@ -156,7 +156,7 @@ __global__ void k_rope_table(float2* tab, int cap, int hd, double theta, RopeSca
 __global__ __launch_bounds__(256) void k_embed(const uint16_t* E, int n_strips, int d, const FwdDesc* desc,
                                                float* x, const float* g, uint16_t* xg, int act_rows, float* ss,
                                                int ss_stride, unsigned long long* t_start, int* fuse_cnt,
-                                               int n_sets, int* ovf) {
+                                               int n_sets, int* ovf, const int* ids) {
   __shared__ float wsum[4];
   const int r = blockIdx.x;
   if (r == 0 && threadIdx.x == 0 && t_start) *t_start = wall_clock64();
@@ -169,7 +169,7 @@ __global__ __launch_bounds__(256) void k_embed(const uint16_t* E, int n_strips, 
                          __HIP_MEMORY_SCOPE_AGENT);
   }
   if (r >= desc->n_rows) return;
-  const int id = desc->ids[r];
+  const int id = ids ? ids[r] : desc->ids[r];   // (ids: a linear pass)
   const size_t strip = (size_t)(id >> 4);
   float sq = 0.f;
   bool bad = false;
@@ -242,9 +242,10 @@ hipError_t launch_rope_table(float2* tab, int cap, int hd, double theta, const R
 
 hipError_t launch_embed(const uint16_t* E, int n_strips, int d, const FwdDesc* desc, float* x, const float* g,
                         uint16_t* xg, int act_rows, float* ss, int ss_stride, int max_rows,
-                        unsigned long long* t_start, int* fuse_cnt, int n_sets, int* ovf, hipStream_t st) {
+                        unsigned long long* t_start, int* fuse_cnt, int n_sets, int* ovf, const int* ids,
+                        hipStream_t st) {
   k_embed<<<max_rows, 256, 0, st>>>(E, n_strips, d, desc, x, g, xg, act_rows, ss, ss_stride, t_start, fuse_cnt,
-                                    n_sets, ovf);
+                                    n_sets, ovf, ids);
   return hipGetLastError();
 }
 

@@ -21,14 +21,11 @@ using namespace pard;
 
 namespace {
 
-constexpr int kPrefillRows = kMaxPassRows;   // prefill chunks run the row-block GEMM
 constexpr int kDescRing = 128;
 constexpr int kStepsPerPlan = 32;            // fused steps between two host checks of the length class
-constexpr int kRowsSplitTarget = 224;       // workgroups a split row-block GEMM aims at (batch-32 step: 224 ahead of 192 and 256)
 constexpr int kLmStrips = 8;                 // strips per lm_head workgroup at up to 16 lm rows
 constexpr int kGatherMax = 4096;
-constexpr size_t kRowsPartBudget = 512;   // fp32 partial tiles of split row-block GEMMs (144 KiB each)
-static_assert(kRowsPartBudget * kRowsPartFloats >= kSplitPartFloats, "split partial tiles share the row-block buffer");
+static_assert(kRowsPartTotal >= kSplitPartFloats, "split partial tiles share the row-block buffer");
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 int ceil_div(int a, int b) { return (a + b - 1) / b; }
@@ -135,34 +132,9 @@ int plan_nw(const GemmPlan& p, int S, int mt) {
   return nw;
 }
 
-// Row-block GEMM plan (passes of more than kMaxRows rows): the grid covers
-// the row bound; narrow shapes split the input dimension so that about 256
-// workgroups work at the typical row count, with the partial tiles in budget.
-struct RowsPlan {
-  int n_tiles = 0, m_blocks = 0, ksplit = 1;
-};
-
-RowsPlan plan_rows(const GemmPlan& p, int max_rows, int typ_rows) {
-  RowsPlan r;
-  r.n_tiles = ceil_div(p.n_strips, kRowsTileStrips);
-  r.m_blocks = ceil_div(max_rows, kRowTiles * 16);
-  const int live = r.n_tiles * ceil_div(std::max(1, std::min(typ_rows, max_rows)), kRowTiles * 16);
-  if (live < 160) r.ksplit = ceil_div(kRowsSplitTarget, live);
-  r.ksplit = std::min({r.ksplit, 16, std::max(1, p.kb_total / 8)});
-  while (r.ksplit > 1 && (size_t)r.ksplit * r.n_tiles * r.m_blocks > kRowsPartBudget) --r.ksplit;
-  return r;
-}
-
-// Tiles that write row sums of squares per residual GEMM (the consumers'
-// ss_tiles) for passes served by the skinny or the row-block GEMM.
-int resid_ss_tiles(const GemmPlan& p, bool rows) {
-  return rows ? ceil_div(p.n_strips, kRowsTileStrips) * kRowsWaves : p.n_strips / pick_S(EPI_RESID, p.n_strips, 1);
-}
-
-// (max, argmax) entries per lm row.
-int lm_entries(const GemmPlan& p, bool rows, int mt) {
-  return rows ? ceil_div(p.n_strips, kRowsTileStrips) * kRowsWaves : p.n_strips / pick_S(EPI_LOGITS, p.n_strips, mt);
-}
+// Tiles that write row sums of squares per residual GEMM of a pass served by
+// the skinny GEMM (its consumers' ss_tiles).
+int resid_ss_tiles(const GemmPlan& p) { return p.n_strips / pick_S(EPI_RESID, p.n_strips, 1); }
 
 struct Layer {
   uint16_t *wqkv = nullptr, *wo = nullptr, *wgu = nullptr, *wd = nullptr;
@@ -179,9 +151,9 @@ struct ModelDev {
   float* g_final = nullptr;
   uint16_t *kcache = nullptr, *vcache = nullptr;
   float2* rope = nullptr;
-  float* x = nullptr;                 // residual stream, fp32 [kMaxPassRows][d]
+  float* x = nullptr;                 // residual stream, fp32 [pass rows][d]
   uint16_t* xg = nullptr;             // x * g of the next normalised GEMM (fp16, k-blocked)
-  float* ss = nullptr;                // per-tile row sums of squares of x [kMaxPassRows][ss_tiles_max]
+  float* ss = nullptr;                // per-tile row sums of squares of x [pass rows][ss_tiles_max]
   int ss_tiles_max = 1;               // ss buffer tiles
   uint16_t *q = nullptr, *attn = nullptr, *h = nullptr;
   float* logits = nullptr;            // lm rows of the last pass [kMaxLmRows][vocab]
@@ -251,6 +223,10 @@ struct pard_ctx {
   size_t kv_seq_stride[2] = {0, 0};
   size_t kv_elems[2] = {0, 0};
   int kv_cap = 0;                       // KV capacity per sequence, max_ctx rounded up to 32
+  int pass_rows = kMaxPassRows;         // rows of the activation buffers: the longest prefill chunk
+  int* ids_dev = nullptr;               // token ids of linear passes [max_ctx], filled in turn
+  int* h_ids = nullptr;                 // their pinned staging, same places
+  int ids_at = 0;                       // first free place since the last synchronisation
   int lm_rows_cap = 0;                  // lm rows of one pass
 };
 
@@ -345,7 +321,8 @@ void derive(ModelDev& M, const pard_model_spec& s, int max_ctx) {
   M.p_gu = plan_gemm(EPI_SWIGLU, 2 * M.f_pad, M.d);
   M.p_d = plan_gemm(EPI_RESID, M.d, M.f_pad);
   M.p_lm = plan_gemm(EPI_LOGITS, s.vocab, M.d);
-  M.ss_tiles_max = std::max(resid_ss_tiles(M.p_o, false), resid_ss_tiles(M.p_o, true));
+  // (the row-block GEMM's tiles are at least two strips wide)
+  M.ss_tiles_max = std::max(resid_ss_tiles(M.p_o), ceil_div(M.p_o.n_strips, 2));
 }
 
 // Lays out (base == nullptr: sizes) every device region of a context.
@@ -356,6 +333,17 @@ size_t layout(pard_ctx* c, char* base) {
   // lm rows of one pass: K + 1 per sequence of a batched step (or a prefill row)
   const int lm_rows_cap = std::min(kMaxLmRows, std::min(c->max_batch, kMaxPassSeqs) * (c->max_k + 1));
   c->lm_rows_cap = lm_rows_cap;
+  // prefill chunks: as long as the context allows up to kMaxPrefillRows, a
+  // multiple of 256 rows, with the activations' byte offsets in 31 bits
+  c->pass_rows = kMaxPassRows;
+  while (c->pass_rows < std::min(kMaxPrefillRows, c->max_ctx)) {
+    bool fits = true;
+    for (const ModelDev& M : c->m)
+      fits = fits && (int64_t)(c->pass_rows + 256) * std::max({M.f_pad, M.q_dim, M.d}) * 2 < (1ll << 31);
+    if (!fits) break;
+    c->pass_rows += 256;
+  }
+  const size_t rows = c->pass_rows;
   size_t attn_part = 1;
   const int cap = c->kv_cap;
   for (int w = 0; w < 2; ++w) {
@@ -381,12 +369,12 @@ size_t layout(pard_ctx* c, char* base) {
     M.kcache = b.take<uint16_t>(kv);
     M.vcache = b.take<uint16_t>(kv);
     M.rope = b.take<float2>((size_t)cap * s.head_dim / 2);
-    M.x = b.take<float>((size_t)kMaxPassRows * M.d);
-    M.xg = b.take<uint16_t>((size_t)kMaxPassRows * M.d);
-    M.ss = b.take<float>((size_t)std::max(1, M.ss_tiles_max) * kMaxPassRows);
-    M.q = b.take<uint16_t>((size_t)kMaxPassRows * M.q_dim);
-    M.attn = b.take<uint16_t>((size_t)kMaxPassRows * M.q_dim);
-    M.h = b.take<uint16_t>((size_t)kMaxPassRows * M.f_pad);
+    M.x = b.take<float>(rows * M.d);
+    M.xg = b.take<uint16_t>(rows * M.d);
+    M.ss = b.take<float>((size_t)std::max(1, M.ss_tiles_max) * rows);
+    M.q = b.take<uint16_t>(rows * M.q_dim);
+    M.attn = b.take<uint16_t>(rows * M.q_dim);
+    M.h = b.take<uint16_t>(rows * M.f_pad);
     M.logits = b.take<float>((size_t)lm_rows_cap * s.vocab);
     M.result = b.take<int>(kMaxLmRows);
     M.lm_map = b.take<int2>(c->max_batch);
@@ -399,7 +387,8 @@ size_t layout(pard_ctx* c, char* base) {
   c->amax_idx = b.take<int>((size_t)max_lm_tiles * lm_rows_cap);
   c->amax_sum = b.take<float>((size_t)max_lm_tiles * lm_rows_cap);
   c->attn_part = b.take<float>(attn_part);
-  c->rows_part = b.take<float>(kRowsPartBudget * kRowsPartFloats);
+  c->rows_part = b.take<float>(kRowsPartTotal);
+  c->ids_dev = b.take<int>(c->max_ctx);
   c->split_counters = b.take<int>(kSplitCounters);
   c->seq_dev = b.take<SeqState>(c->max_batch);
   c->out_dev = b.take<int>((size_t)c->max_batch * c->max_ctx);
@@ -590,11 +579,12 @@ struct PassSpec {
   int tail = TAIL_NONE;
   FwdDesc* next_desc = nullptr;
   bool emit = false;
+  const int* ids = nullptr;  // token ids of a linear pass (device)
 };
 
 // One GEMM of a pass: the skinny kernel up to kMaxRows rows, the row-block
-// kernel above.
-hipError_t run_gemm(pard_ctx* c, int cls, int epi, int max_rows, int typ_rows, GemmArgs a, const GemmPlan& p) {
+// kernel (plan r) above.
+hipError_t run_gemm(pard_ctx* c, int cls, int epi, int max_rows, const RowsPlan& r, GemmArgs a, const GemmPlan& p) {
   // a timed GEMM launch carries its events: they take the kernel's own start
   // and end timestamps, not those of separate marker packets
   LaunchEvents ev;
@@ -606,12 +596,11 @@ hipError_t run_gemm(pard_ctx* c, int cls, int epi, int max_rows, int typ_rows, G
   a.kb_total = p.kb_total;
   a.n_strips = p.n_strips;
   if (max_rows > kMaxRows) {
-    const RowsPlan r = plan_rows(p, max_rows, typ_rows > 0 ? typ_rows : max_rows);
     a.n_tiles = r.n_tiles;
     a.m_blocks = r.m_blocks;
     a.ksplit = r.ksplit;
     a.part = c->rows_part;
-    return launch_gemm_rows(epi, a, c->stream, ev);
+    return launch_gemm_rows(epi, r.variant, a, c->stream, ev);
   }
   const int mt = ceil_div(max_rows, 16);
   const int S = pick_S(epi, p.n_strips, mt);
@@ -628,10 +617,22 @@ pard_status forward(pard_ctx* c, int w, const PassSpec& ps) {
   const pard_model_spec& s = M.spec;
   const bool rows = ps.max_rows > kMaxRows;
   const int typ = ps.typ_rows > 0 ? ps.typ_rows : ps.max_rows;
-  const int ss_tiles = resid_ss_tiles(M.p_o, rows);
-  const int act_rows = rows ? kMaxPassRows : kMaxRows;
+  const int act_rows = !rows ? kMaxRows : ps.ids ? c->pass_rows : kMaxPassRows;
   const int cls0 = w * 8;
-  if (ps.max_rows < 1 || ps.max_rows > kMaxPassRows || ps.n_seq < 1 || ps.n_seq > kMaxPassSeqs ||
+  // row-block plans of the pass's GEMMs; the row sums of squares of the
+  // residual GEMMs come in their plan's pieces
+  RowsPlan r_qkv, r_o, r_gu, r_d;
+  int ss_o = resid_ss_tiles(M.p_o), ss_d = resid_ss_tiles(M.p_d);
+  if (rows) {
+    auto plan = [&](const GemmPlan& p) { return plan_rows(p.n_strips, p.kb_total, ps.max_rows, typ); };
+    r_qkv = plan(M.p_qkv);
+    r_o = plan(M.p_o);
+    r_gu = plan(M.p_gu);
+    r_d = plan(M.p_d);
+    ss_o = r_o.entries;
+    ss_d = r_d.entries;
+  }
+  if (ps.max_rows < 1 || ps.max_rows > (ps.ids ? c->pass_rows : kMaxPassRows) || ps.n_seq < 1 || ps.n_seq > kMaxPassSeqs ||
       ps.max_lm_rows > c->lm_rows_cap)
     return fail(c, PARD_ERR_CAPACITY, "pass of %d rows / %d sequences exceeds the engine's limits", ps.max_rows,
                 ps.n_seq);
@@ -639,7 +640,7 @@ pard_status forward(pard_ctx* c, int w, const PassSpec& ps) {
     Timed t(c, cls0 + 0);
     HIP_TRY(c, launch_embed(M.embed, M.p_lm.n_strips, M.d, M.desc, M.x, M.layers[0].g_attn, M.xg, act_rows, M.ss,
                             std::max(1, M.ss_tiles_max), ps.max_rows, &c->clock_dev->pass_start[w],
-                            fuse_counters(c, w), s.n_layers, M.ovf, c->stream));
+                            fuse_counters(c, w), s.n_layers, M.ovf, ps.ids, c->stream));
   }
   const size_t layer_kv = (size_t)s.n_kv_heads * c->kv_cap * s.head_dim;
   // attention plan: one workgroup per (sequence, KV head, query group, key
@@ -658,8 +659,6 @@ pard_status forward(pard_ctx* c, int w, const PassSpec& ps) {
   int nqt = std::min(attn_max_q_tiles(s.head_dim), ceil_div(qpairs, 16));
   if (wide) nqt = std::min(nqt, s.head_dim == 128 ? 1 : kAttnWideQTiles64);
   const int n_qblocks = ceil_div(qpairs, 16 * nqt);
-  if (ps.n_seq * n_qblocks > kAttnRecords)
-    return fail(c, PARD_ERR_CAPACITY, "attention plan: %d query blocks exceed the record budget", ps.n_seq * n_qblocks);
   int split_len = wide ? ceil_div(l_bound, 128) * 128 : kAttnChunk;
   // row-block passes over several sequences (batched decode): 1024-key
   // chunks (batch-32 step 15.5 ms with 256, 15.4 with 512, 15.2 with 1024;
@@ -673,7 +672,8 @@ pard_status forward(pard_ctx* c, int w, const PassSpec& ps) {
     const int per = std::max(1, kAttnDecodeWGs / (ps.n_seq * s.n_kv_heads * n_qblocks));
     split_len = std::min(kAttnLongChunkMax, std::max(split_len, ceil_div(ceil_div(l_bound, per), 128) * 128));
   }
-  while ((int64_t)ps.n_seq * n_qblocks * ceil_div(l_bound, split_len) > kAttnRecords) split_len *= 2;
+  // (one chunk writes no records)
+  while (split_len < l_bound && (int64_t)ps.n_seq * n_qblocks * ceil_div(l_bound, split_len) > kAttnRecords) split_len *= 2;
   const int n_splits = ceil_div(l_bound, split_len);
   // decode passes over one attention chunk: QKV GEMM and attention in one
   // launch when its grid fits the device at once
@@ -760,7 +760,7 @@ pard_status forward(pard_ctx* c, int w, const PassSpec& ps) {
       a.A = M.xg;
       a.lda = M.d;
       a.ss_in = M.ss;
-      a.ss_tiles = l == 0 ? 1 : ss_tiles;
+      a.ss_tiles = l == 0 ? 1 : ss_d;
       a.out = M.q;
       a.ld_out = M.q_dim;
       a.kc = kc;
@@ -785,7 +785,7 @@ pard_status forward(pard_ctx* c, int w, const PassSpec& ps) {
         f.n_cons = n_attn_wg;
         GemmArgs o{}, gu{}, dn{};
         if (fused_o) o = o_args(M, L, act_rows);
-        if (fused_gu) gu = gu_args(M, L, act_rows, ss_tiles, S_gu);
+        if (fused_gu) gu = gu_args(M, L, act_rows, ss_o, S_gu);
         if (fused_d) dn = d_args(M, l, act_rows, true, c->rows_part, c->split_counters);
         // the kernel timer's QKV class covers the fused launch (attention included)
         LaunchEvents ev;
@@ -797,7 +797,7 @@ pard_status forward(pard_ctx* c, int w, const PassSpec& ps) {
         HIP_TRY(c, launch_qkv_attn(mt_q, S_q, s.head_dim, a, aa, f, fused_o ? &o : nullptr, fused_gu ? &gu : nullptr,
                                    S_gu, fused_d ? &dn : nullptr, c->stream, ev));
       } else {
-        HIP_TRY(c, run_gemm(c, cls0 + 1, EPI_QKV, ps.max_rows, typ, a, M.p_qkv));
+        HIP_TRY(c, run_gemm(c, cls0 + 1, EPI_QKV, ps.max_rows, r_qkv, a, M.p_qkv));
       }
     }
     if (!fused) {  // attention
@@ -805,32 +805,35 @@ pard_status forward(pard_ctx* c, int w, const PassSpec& ps) {
       HIP_TRY(c, launch_attention(s.head_dim, aa, c->stream));
     }
     if (!fused_o) {  // O-projection + residual
-      HIP_TRY(c, run_gemm(c, cls0 + 3, EPI_RESID, ps.max_rows, typ, o_args(M, L, act_rows), M.p_o));
+      HIP_TRY(c, run_gemm(c, cls0 + 3, EPI_RESID, ps.max_rows, r_o, o_args(M, L, act_rows), M.p_o));
     }
     if (!fused_gu) {  // norm + gate/up + SiLU * up
-      HIP_TRY(c, run_gemm(c, cls0 + 4, EPI_SWIGLU, ps.max_rows, typ, gu_args(M, L, act_rows, ss_tiles, 0), M.p_gu));
+      HIP_TRY(c, run_gemm(c, cls0 + 4, EPI_SWIGLU, ps.max_rows, r_gu, gu_args(M, L, act_rows, ss_o, 0), M.p_gu));
     }
     if (!fused_d) {  // down + residual
-      HIP_TRY(c, run_gemm(c, cls0 + 5, EPI_RESID, ps.max_rows, typ, d_args(M, l, act_rows, false, nullptr, nullptr),
+      HIP_TRY(c, run_gemm(c, cls0 + 5, EPI_RESID, ps.max_rows, r_d, d_args(M, l, act_rows, false, nullptr, nullptr),
                           M.p_d));
     }
   }
   if (ps.max_lm_rows > 0) {
     const bool lm_rows = ps.max_lm_rows > kMaxRows;
     const int mt_lm = ceil_div(ps.max_lm_rows, 16);
+    const int S_lm = pick_S(EPI_LOGITS, M.p_lm.n_strips, mt_lm);
+    RowsPlan r_lm;
+    if (lm_rows) r_lm = plan_rows(M.p_lm.n_strips, M.p_lm.kb_total, ps.max_lm_rows, std::min(typ, ps.max_lm_rows));
     GemmArgs a = gemm_base(M, M.lm_head, act_rows);
     a.A = M.xg;
     a.lda = M.d;
     a.ss_in = M.ss;
-    a.ss_tiles = ss_tiles;
+    a.ss_tiles = ss_d;
     a.logits = M.logits;
     a.vocab = s.vocab;
     a.amax_val = c->amax_val;
     a.amax_idx = c->amax_idx;
-    a.amax_stride = lm_entries(M.p_lm, lm_rows, mt_lm);
+    a.amax_stride = lm_rows ? r_lm.entries : M.p_lm.n_strips / S_lm;   // (max, argmax) entries per lm row
     a.samp_k = c->samp_k;
     a.amax_sum = c->amax_sum;
-    HIP_TRY(c, run_gemm(c, cls0 + 6, EPI_LOGITS, ps.max_lm_rows, ps.max_lm_rows, a, M.p_lm));
+    HIP_TRY(c, run_gemm(c, cls0 + 6, EPI_LOGITS, ps.max_lm_rows, r_lm, a, M.p_lm));
     TailArgs ta{};
     ta.desc = M.desc;
     ta.amax_val = c->amax_val;
@@ -850,7 +853,7 @@ pard_status forward(pard_ctx* c, int w, const PassSpec& ps) {
     ta.amax_sum = c->amax_sum;
     ta.logits = M.logits;
     ta.q_logits = c->m[PARD_DRAFT].logits;
-    ta.tile_w = lm_rows ? kRowsWaveStrips * 16 : pick_S(EPI_LOGITS, M.p_lm.n_strips, mt_lm) * 16;
+    ta.tile_w = (lm_rows ? r_lm.ent_strips : S_lm) * 16;
     ta.clock = c->clock_dev;
     Timed t(c, cls0 + 7);
     HIP_TRY(c, launch_tail(ta, ps.n_seq, c->stream));
@@ -883,6 +886,7 @@ pard_status pull_seqs_sync(pard_ctx* c, const int* seqs, int n) {
   HIP_TRY(c, hipMemcpyAsync(c->h_fuse_err, c->fuse_err, sizeof(int) * 64, hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   c->desc_slot = 0;
+  c->ids_at = 0;
   if (c->h_fuse_err[0])
     return fail(c, PARD_ERR_DEVICE, "a QKV+attention launch's wait exceeded its spin limit: results are invalid");
   if (c->h_fuse_err[32]) {
@@ -928,19 +932,70 @@ FwdDesc make_desc(int slot, const int* ids, int n_ids, int n_masks, int mask_id,
   return d;
 }
 
-// Ingest tokens[0..n) at positions pos0.. into model w's cache of one slot (no lm_head).
-pard_status ingest(pard_ctx* c, int w, int seq, const int* tokens, int n, int pos0) {
-  for (int off = 0; off < n; off += kPrefillRows) {
-    const int rows = std::min(kPrefillRows, n - off);
-    pard_status st = stage_desc(c, w, make_desc(seq, tokens + off, rows, 0, 0, pos0 + off, rows, rows - 1, 1));
-    if (st != PARD_OK) return st;
+// Copies n token ids (at most max_ctx) to the device for linear passes; *out:
+// their device address, valid until the stream is synchronised and another
+// call comes.
+pard_status stage_ids(pard_ctx* c, const int* tokens, int n, const int** out) {
+  if (c->ids_at + n > c->max_ctx) {
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    c->ids_at = 0;
+  }
+  memcpy(c->h_ids + c->ids_at, tokens, sizeof(int) * n);
+  HIP_TRY(c, hipMemcpyAsync(c->ids_dev + c->ids_at, c->h_ids + c->ids_at, sizeof(int) * n, hipMemcpyHostToDevice,
+                            c->stream));
+  *out = c->ids_dev + c->ids_at;
+  c->ids_at += n;
+  return PARD_OK;
+}
+
+// One model's passes over n tokens (ids; d_ids: the same on the device) at
+// positions pos0.. of one slot, in chunks of pass_rows rows or, where several
+// are needed, as even ones (so none is a few rows that stream all weights).
+// lm: the last chunk's last row goes through the lm_head and sets the slot's
+// first token.
+pard_status prefill_passes(pard_ctx* c, int w, int seq, const int* ids, const int* d_ids, int n, int pos0, bool lm) {
+  const int n_chunks = ceil_div(n, c->pass_rows);
+  const int per = std::min(c->pass_rows, ceil_div(ceil_div(n, n_chunks), 128) * 128);
+  for (int off = 0; off < n; off += per) {
+    const int rows = std::min(per, n - off);
+    FwdDesc d{};
     PassSpec ps;
+    if (rows > kMaxRows) {
+      PassSeq& q = d.seq[0];
+      q.slot = seq;
+      q.n_rows = q.n_real = rows;
+      q.pos0 = pos0 + off;
+      q.lm_rows = 1;
+      d.n_rows = rows;
+      d.n_seq = 1;
+      d.n_lm = 1;
+      d.linear = 1;
+      d.lm_src[0] = rows - 1;
+      ps.ids = d_ids + off;
+    } else {
+      d = make_desc(seq, ids + off, rows, 0, 0, pos0 + off, rows, rows - 1, 1);
+    }
+    pard_status st = stage_desc(c, w, d);
+    if (st != PARD_OK) return st;
     ps.max_rows = rows;
     ps.l_bound = pos0 + off + rows;
-    st = forward(c, w, ps);
-    if (st != PARD_OK) return st;
+    if (lm && off + rows == n) {
+      ps.max_lm_rows = 1;
+      ps.tail = TAIL_PREFILL;
+    }
+    if ((st = forward(c, w, ps)) != PARD_OK) return st;
   }
   return PARD_OK;
+}
+
+// Ingest tokens[0..n) at positions pos0.. into model w's cache of one slot (no lm_head).
+pard_status ingest(pard_ctx* c, int w, int seq, const int* tokens, int n, int pos0) {
+  const int* d_ids = nullptr;
+  if (n > kMaxRows) {
+    const pard_status st = stage_ids(c, tokens, n, &d_ids);
+    if (st != PARD_OK) return st;
+  }
+  return prefill_passes(c, w, seq, tokens, d_ids, n, pos0, false);
 }
 
 bool ids_ok(const int* ids, int n, int vocab) {
@@ -991,7 +1046,7 @@ pard_status step_passes(pard_ctx* c, const StepShape& sh) {
   } else if (K > 0) {
     PassSpec pd;
     pd.max_rows = sh.draft_rows;
-    pd.typ_rows = n * K;
+    pd.typ_rows = n * (K + 1);   // about one accepted candidate a step
     pd.max_lm_rows = n * K;
     pd.n_seq = n;
     pd.max_seq_rows = n > 1 ? 2 * K : sh.draft_rows;
@@ -1129,6 +1184,7 @@ pard_status pard_model_load(const pard_model_spec* target, const pard_model_spec
       hipHostMalloc((void**)&c->h_gather_idx, sizeof(size_t) * kGatherMax, hipHostMallocDefault) != hipSuccess ||
       hipHostMalloc((void**)&c->h_gather_out, sizeof(float) * kGatherMax, hipHostMallocDefault) != hipSuccess ||
       hipHostMalloc((void**)&c->h_out, sizeof(int) * max_ctx, hipHostMallocDefault) != hipSuccess ||
+      hipHostMalloc((void**)&c->h_ids, sizeof(int) * max_ctx, hipHostMallocDefault) != hipSuccess ||
       hipHostMalloc((void**)&c->h_clock, sizeof(PhaseClock), hipHostMallocDefault) != hipSuccess ||
       hipHostMalloc((void**)&c->h_fuse_err, sizeof(int) * 64, hipHostMallocDefault) != hipSuccess)
     return bail(PARD_ERR_DEVICE);
@@ -1184,6 +1240,7 @@ void pard_free(pard_ctx* c) {
   if (c->h_gather_idx) (void)hipHostFree(c->h_gather_idx);
   if (c->h_gather_out) (void)hipHostFree(c->h_gather_out);
   if (c->h_out) (void)hipHostFree(c->h_out);
+  if (c->h_ids) (void)hipHostFree(c->h_ids);
   if (c->h_clock) (void)hipHostFree(c->h_clock);
   if (c->h_fuse_err) (void)hipHostFree(c->h_fuse_err);
   if (c->ev_start) (void)hipEventDestroy(c->ev_start);
@@ -1225,22 +1282,10 @@ pard_status pard_prefill(pard_ctx* c, int32_t seq, const int32_t* prompt, int32_
   S.L[1] = n;
   S.mask_id = c->mask_id;
   if ((st = push_seq(c, seq)) != PARD_OK) return st;
-  for (int w = 1; w >= 0; --w) {   // draft first, the target's last chunk sets the first token
-    for (int off = 0; off < n; off += kPrefillRows) {
-      const int rows = std::min(kPrefillRows, n - off);
-      const bool last = (off + rows == n) && w == PARD_TARGET;
-      st = stage_desc(c, w, make_desc(seq, prompt + off, rows, 0, 0, off, rows, rows - 1, 1));
-      if (st != PARD_OK) return st;
-      PassSpec ps;
-      ps.max_rows = rows;
-      ps.l_bound = off + rows;
-      if (last) {
-        ps.max_lm_rows = 1;
-        ps.tail = TAIL_PREFILL;
-      }
-      if ((st = forward(c, w, ps)) != PARD_OK) return st;
-    }
-  }
+  const int* d_ids = nullptr;
+  if (n > kMaxRows && (st = stage_ids(c, prompt, n, &d_ids)) != PARD_OK) return st;
+  for (int w = 1; w >= 0; --w)   // draft first, the target's last chunk sets the first token
+    if ((st = prefill_passes(c, w, seq, prompt, d_ids, n, 0, w == PARD_TARGET)) != PARD_OK) return st;
   if ((st = pull_seq_sync(c, seq)) != PARD_OK) return st;
   *first_token = S.bonus;
   c->hist[seq].assign(prompt, prompt + n);

@@ -42,6 +42,7 @@
 // step tail: candidates for a draft pass; greedy prefix acceptance, KV
 // rollback and next-pass staging for a verify pass.
 #include "attn_tile.h"
+#include "gemm_util.h"
 #include "pard_internal.h"
 
 #include <hip/hip_ext.h>
@@ -49,34 +50,9 @@
 #include <algorithm>
 #include <climits>
 #include <map>
-#include <type_traits>
 
 namespace pard {
 namespace {
-
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-
-
-constexpr int kRsrcWord3 = 0x00020000;   // buffer descriptor word 3 for gfx9-family raw buffers
-constexpr int kCachePolicyNT = 2;        // non-temporal: weights are streamed once
-constexpr int kWaitVmcnt0 = 0x0F70;      // s_waitcnt vmcnt(0), expcnt and lgkmcnt not waited for
-
-// Sum over the 16 lanes of a DPP row (lanes 16g .. 16g+15), fixed order:
-// quad_perm swaps (1 0 3 2), (2 3 0 1), then half-row and row mirrors.
-__device__ __forceinline__ float sum16(float x) {
-  x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0xB1, 0xF, 0xF, false));
-  x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x4E, 0xF, 0xF, false));
-  x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x141, 0xF, 0xF, false));
-  x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x140, 0xF, 0xF, false));
-  return x;
-}
-
-__device__ __forceinline__ bool better(float v, int i, float bv, int bi) {
-  return v > bv || (v == bv && i < bi);
-}
 
 // Wavefront reductions and scan in a fixed order (results do not depend on timing).
 __device__ __forceinline__ float wave_sum(float v) {
@@ -1115,6 +1091,7 @@ __device__ void stage_next(const TailArgs& p, bool drop_done) {
     nd->n_rows = r0[n];
     nd->n_seq = n;
     nd->n_lm = l0[n];
+    nd->linear = 0;
   }
 }
 
@@ -1476,521 +1453,6 @@ __global__ __launch_bounds__(256) void k_stage(const TailArgs p) {
   }
 }
 
-// ============================================================================
-// Row-block GEMM: passes of more than kMaxRows rows (batched decode passes,
-// where the GEMMs are dense contractions at a few hundred rows).
-//
-// A workgroup of kRowsWaves wavefronts owns kRowTiles*16 (144) rows x 16
-// strips (256 columns) over one input range.  The block's rows of A pass
-// through LDS one k-block (9 KiB) at a time and are shared by the wavefronts;
-// each wavefront streams its own 4 strips of W from HBM straight into the MFMA
-// B-operand registers and accumulates 9 x 4 tiles of 16x16 (per k-block:
-// 9 KiB of LDS reads and 4 KiB of weights for 36 MFMAs).  The k-blocks are
-// software-pipelined (loads 4 k-blocks ahead, A through LDS 2 ahead and into
-// fragment registers 1 ahead), so the MFMAs of a k-block wait on nothing
-// requested in the same iteration.  Row tiles past the pass's
-// rows skip their MFMAs; row blocks past them leave at once.
-//
-// Blocks are numbered so that the row blocks of one column tile run on the
-// same XCD at about the same time (the hardware deals block i to XCD i % 8):
-// the later blocks' weight reads then hit that XCD's L2 rather than HBM.
-// Narrow GEMMs split the input dimension (ksplit > 1) to fill the chip; each
-// split writes an fp32 partial tile and k_gemm_rows_red adds them in split
-// order and runs the epilogue, so results are deterministic.
-// ============================================================================
-
-typedef f32x4 RowsAcc[kRowTiles][kRowsWaveStrips];
-
-// Compile-time loop: f(integral_constant<int, I>) for I in [B, E).  The row
-// tiles of an accumulator are walked this way so that every index is a
-// constant whatever the loop body's size: the accumulators then stay in
-// registers (a rolled loop would index them dynamically, in scratch memory).
-template <int B, int E, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (B < E) {
-    f(std::integral_constant<int, B>{});
-    static_for<B + 1, E>(f);
-  }
-}
-
-// 1/rms of the block's rows from the producer's per-tile sums of squares
-// (fixed order), 16 threads per row.
-template <bool LM>
-__device__ __forceinline__ void rows_scales(const GemmArgs& p, const FwdDesc* dp, int row0, int row_count, float* rs_s,
-                                            int mt_only = -1) {
-  // 16 threads per row, rows tid / 16 + 16 k: every row's loads are in flight
-  // together (one round of loads per 64 tiles, not one per row), each thread
-  // adding its tiles in increasing order.  mt_only >= 0: the rows of that row
-  // tile only (rs_s entries of the others are not written).
-  const int tid = threadIdx.x;
-  constexpr int R = kRowTiles;                     // rows per thread group
-  int src[R];
-  float t[R];
-#pragma unroll
-  for (int k = 0; k < R; ++k) {
-    const int gr = row0 + (tid >> 4) + 16 * (mt_only >= 0 ? mt_only : k);
-    src[k] = gr < row_count ? (LM ? dp->lm_src[gr] : gr) : 0;
-    t[k] = 0.f;
-  }
-  const int n_k = mt_only >= 0 ? 1 : R;            // uniform
-  for (int q0 = tid & 15; q0 < p.ss_tiles; q0 += 64) {
-    float part[R][4];
-#pragma unroll
-    for (int k = 0; k < R; ++k)
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int q = q0 + 16 * u;
-        part[k][u] = q < p.ss_tiles && k < n_k ? p.ss_in[(size_t)src[k] * p.ss_stride + q] : 0.f;
-      }
-#pragma unroll
-    for (int k = 0; k < R; ++k)
-#pragma unroll
-      for (int u = 0; u < 4; ++u) t[k] += part[k][u];
-  }
-#pragma unroll
-  for (int k = 0; k < R; ++k) {
-    float v = t[k];
-    v += __shfl_xor(v, 8);
-    v += __shfl_xor(v, 4);
-    v += __shfl_xor(v, 2);
-    v += __shfl_xor(v, 1);
-    if ((tid & 15) == 0 && k < n_k) rs_s[(tid >> 4) + 16 * (mt_only >= 0 ? mt_only : k)] = 1.0f / sqrtf(v * p.inv_k + p.eps);
-  }
-}
-
-// Epilogue of one wavefront's accumulators, row tiles [mt_lo, mt_live).  Lane
-// l holds, for row tile mt and strip s, column (strip*16 + l%16) of rows
-// mt*16 + 4*(l/16) + i.
-template <int EPI>
-__device__ __forceinline__ void rows_epilogue(const GemmArgs& p, const FwdDesc* dp, RowsAcc& acc, int tile, int row0,
-                                              int row_count, int mt_lo, int mt_live, int wave, int lane,
-                                              const float* rs_s, u32x4* o_lds = nullptr) {
-  const int c16 = lane & 15, g4 = lane >> 4;
-  const int strip0 = tile * kRowsTileStrips + wave * kRowsWaveStrips;
-  [[maybe_unused]] bool bad = false;
-  if constexpr (EPI == EPI_QKV) {
-    static_for<0, kRowTiles>([&](auto mtc) __attribute__((always_inline)) {
-      constexpr int mt = decltype(mtc)::value;
-      if (mt < mt_lo || mt >= mt_live) return;       // uniform
-#pragma unroll
-      for (int s = 0; s < kRowsWaveStrips; ++s) {
-        const int n = (strip0 + s) * 16 + c16;
-        const bool col_ok = strip0 + s < p.n_strips;
-        const float bias = (col_ok && p.bias) ? p.bias[n] : 0.f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int rl = mt * 16 + g4 * 4 + i, r = row0 + rl;
-          float y = acc[mt][s][i] * rs_s[rl] + bias;
-          // rotary partner column (n ^ 1) is in lane l ^ 1 (DPP quad swap)
-          const float partner = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, y), 0xB1,
-                                                                                   0xF, 0xF, false));
-          if (col_ok && r < row_count) {
-            const int pos = dp->pos[r];
-            const size_t cache = (size_t)dp->slot[r] * p.kv_seq_stride;
-            if (n < p.q_dim + p.kv_dim) {
-              const float2 cs = p.rope[(size_t)pos * (p.hd / 2) + ((n % p.hd) >> 1)];
-              y = (n & 1) ? (y * cs.x + partner * cs.y) : (y * cs.x - partner * cs.y);
-            }
-            const uint16_t b = f16_flagged(y, bad);
-            if (n < p.q_dim) {
-              p.out[(size_t)r * p.ld_out + n] = b;
-            } else if (n < p.q_dim + p.kv_dim) {
-              const int c = n - p.q_dim;
-              p.kc[cache + (size_t)(c / p.hd) * p.cap * p.hd + k_index(pos, c % p.hd, p.hd)] = b;
-            } else {
-              const int c = n - p.q_dim - p.kv_dim;
-              const size_t blk = (size_t)(c / p.hd) * (p.cap / 32) + (pos >> 5);
-              p.vc[cache + (blk * p.hd + (c % p.hd)) * 32 + v_slot(pos & 31)] = b;
-            }
-          }
-        }
-      }
-    });
-    flag_range(bad, p.ovf);
-  } else if constexpr (EPI == EPI_RESID) {
-    float* ss = p.ss_out + (tile * kRowsWaves + wave);
-    static_for<0, kRowTiles>([&](auto mtc) __attribute__((always_inline)) {
-      constexpr int mt = decltype(mtc)::value;
-      if (mt < mt_lo || mt >= mt_live) return;       // uniform
-      float sq[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int s = 0; s < kRowsWaveStrips; ++s) {
-        const int n = (strip0 + s) * 16 + c16;
-        if (strip0 + s >= p.n_strips) continue;      // uniform
-        const float g = p.g_next[n];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int r = row0 + mt * 16 + g4 * 4 + i;
-          if (r < row_count) {
-            const size_t o = (size_t)r * p.ldx + n;
-            const float xn = p.x[o] + acc[mt][s][i];   // residual + projection
-            p.x[o] = xn;
-            p.xg[act_index(r, n, p.act_rows)] = f16_flagged(xn * g, bad);
-            sq[i] += xn * xn;
-          }
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float t = sum16(sq[i]);
-        const int r = row0 + mt * 16 + g4 * 4 + i;
-        if (c16 == 0 && r < row_count) ss[(size_t)r * p.ss_stride] = t;
-      }
-    });
-    flag_range(bad, p.ovf);
-  } else if constexpr (EPI == EPI_SWIGLU) {
-    // 8 gate columns then the 8 up columns of the same features per strip.
-    // The wavefront's 4 strips are the 32 features of one k-block of h
-    // (block tile * 4 + wave): with o_lds (this wavefront's 9 KiB) the block
-    // is assembled in LDS and written with 16-byte stores, one row's 64 bytes
-    // per 4 lanes (2-byte stores straight from the accumulator layout made the
-    // epilogue as long as the GEMM); without, each lane stores its values.
-    static_for<0, kRowTiles>([&](auto mtc) __attribute__((always_inline)) {
-      constexpr int mt = decltype(mtc)::value;
-      if (mt < mt_lo || mt >= mt_live) return;       // uniform
-#pragma unroll
-      for (int s = 0; s < kRowsWaveStrips; ++s) {
-        if (strip0 + s >= p.n_strips) continue;      // uniform
-        const int f = (strip0 + s) * 8 + c16;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int rl = mt * 16 + g4 * 4 + i, r = row0 + rl;
-          const float gt = acc[mt][s][i] * rs_s[rl];
-          // the up value of lane l < 8 is in lane l + 8 of its row of 16 (DPP row rotate by 8)
-          const float up = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, gt), 0x128,
-                                                                              0xF, 0xF, false));
-          // silu(g) = g / (1 + e^-g), with the hardware exp2 and reciprocal
-          const float h = gt * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-gt * attn::kLog2e)) * up;
-          bool bad_h = false;
-          const uint16_t hb = f16_flagged(h, bad_h);
-          bad |= bad_h && c16 < 8 && r < row_count;
-          if (o_lds) {
-            // rows rl, chunk s (features s*8 .. s*8+7): lane pairs pack two
-            // values into one dword (DPP quad swap); chunks are swizzled by
-            // (rl / 4) % 4 so the four rows of one store land in different banks
-            const uint32_t pair =
-                (uint32_t)hb | ((uint32_t)__builtin_amdgcn_mov_dpp((int)hb, 0xB1, 0xF, 0xF, false) << 16);
-            if (c16 < 8 && !(c16 & 1))
-              reinterpret_cast<uint32_t*>(o_lds)[(rl * 4 + (s ^ ((rl >> 2) & 3))) * 4 + (c16 >> 1)] = pair;
-          } else if (c16 < 8 && r < row_count) {
-            p.out[act_index(r, f, p.act_rows)] = hb;
-          }
-        }
-      }
-    });
-    if (o_lds) {
-      // this wavefront's rows [row0 + 16 mt_lo, row0 + 16 mt_live) of block tile * 4 + wave
-      const int blk = tile * kRowsWaves + wave;
-      if (blk * 4 < p.n_strips) {                    // uniform: the block holds features of the weight
-        for (int e = mt_lo * 64 + lane; e < mt_live * 64; e += 64) {
-          const int rl = e >> 2, c = e & 3, r = row0 + rl;
-          const u32x4 v = o_lds[rl * 4 + (c ^ ((rl >> 2) & 3))];
-          if (r < row_count)
-            *reinterpret_cast<u32x4*>(p.out + act_index(r, blk * 32 + c * 8, p.act_rows)) = v;
-        }
-      }
-    }
-    flag_range(bad, p.ovf);
-  } else {  // EPI_LOGITS
-    static_for<0, kRowTiles>([&](auto mtc) __attribute__((always_inline)) {
-      constexpr int mt = decltype(mtc)::value;
-      if (mt < mt_lo || mt >= mt_live) return;       // uniform
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int rl = mt * 16 + g4 * 4 + i, r = row0 + rl;
-        float bv = -INFINITY;
-        int bi = INT_MAX;
-#pragma unroll
-        for (int s = 0; s < kRowsWaveStrips; ++s) {
-          const int n = (strip0 + s) * 16 + c16;
-          if (strip0 + s >= p.n_strips) continue;    // uniform
-          const float val = acc[mt][s][i] * rs_s[rl];
-          if (r < row_count) p.logits[(size_t)r * p.vocab + n] = val;
-          if (better(val, n, bv, bi)) { bv = val; bi = n; }
-        }
-#pragma unroll
-        for (int off = 8; off > 0; off >>= 1) {
-          const float ov = __shfl_xor(bv, off);
-          const int oi = __shfl_xor(bi, off);
-          if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
-        }
-        if (c16 == 0 && r < row_count) {
-          p.amax_val[(size_t)r * p.amax_stride + tile * kRowsWaves + wave] = bv;
-          p.amax_idx[(size_t)r * p.amax_stride + tile * kRowsWaves + wave] = bi;
-        }
-        if (p.samp_k > 0.f) {       // sampling: the entry's softmax weight relative to its max
-          float sw = 0.f;
-#pragma unroll
-          for (int s = 0; s < kRowsWaveStrips; ++s) {
-            if (strip0 + s >= p.n_strips) continue;  // uniform
-            sw += __builtin_amdgcn_exp2f((acc[mt][s][i] * rs_s[rl] - bv) * p.samp_k);
-          }
-#pragma unroll
-          for (int off = 8; off > 0; off >>= 1) sw += __shfl_xor(sw, off);
-          if (c16 == 0 && r < row_count) p.amax_sum[(size_t)r * p.amax_stride + tile * kRowsWaves + wave] = sw;
-        }
-      }
-    });
-  }
-}
-
-// Block id -> (column tile, input split, row block), row blocks fastest and
-// consecutive ids on one XCD.
-__device__ __forceinline__ void rows_block(const GemmArgs& p, int* tile, int* ks, int* mb) {
-  const int G = gridDim.x, bid = blockIdx.x;
-  const int per = G / 8, rem = G % 8, xcd = bid % 8, slot = bid / 8;
-  const int lid = xcd * per + min(xcd, rem) + slot;
-  *mb = lid % p.m_blocks;
-  const int rest = lid / p.m_blocks;
-  *ks = rest % p.ksplit;
-  *tile = rest / p.ksplit;
-}
-
-template <int EPI>
-__global__ __launch_bounds__(256) void k_gemm_rows(const GemmArgs p) {
-  constexpr int MB = kRowTiles, NS = kRowsWaveStrips;
-  constexpr int AE = MB * 64;                        // 16-byte A elements of one k-block
-  constexpr int AJ = (AE + 255) / 256;               // per thread
-  constexpr bool LM = EPI == EPI_LOGITS;             // rows are the pass's lm rows
-  // (padded to whole rounds of the workgroup's threads: every thread stores
-  // each of its AJ elements, those past AE are zeros never read)
-  __shared__ __attribute__((aligned(16))) u32x4 a_lds[2][AJ * 256];
-  // SwiGLU: each wavefront's block of h (MB * 16 rows x 64 bytes) for 16-byte stores
-  __shared__ __attribute__((aligned(16))) u32x4 o_lds[EPI == EPI_SWIGLU ? kRowsWaves * MB * 64 : 1];
-  __shared__ float rs_s[MB * 16];
-
-  int tile, ks, mb;
-  rows_block(p, &tile, &ks, &mb);
-  const FwdDesc* dp = p.desc;
-  const int row_count = LM ? dp->n_lm : dp->n_rows;
-  const int row0 = mb * MB * 16;
-  if (row0 >= row_count) return;                     // uniform: the whole block leaves
-  const int mt_live = min(MB, (row_count - row0 + 15) / 16);
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int kb0 = ks * p.kb_total / p.ksplit, kb1 = (ks + 1) * p.kb_total / p.ksplit;
-  const int n_kb = kb1 - kb0;
-
-  // W: this wavefront's strips, block (kb, strip) at (kb * n_strips + strip) KiB
-  const int strip0 = tile * kRowsTileStrips + wave * NS;
-  const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t*>(p.W), 0, (int)min((size_t)p.n_strips * p.kb_total * 1024, (size_t)0x7fffffff),
-      kRsrcWord3);
-  // strips past the weight's last one (only in the last column tile) read
-  // zeros or neighbouring weights: their columns are never stored
-  const int w_voff = (strip0 * 64 + lane) * 16;
-
-  // A: element e of a k-block is 16 bytes of block row e / 4; rows past the
-  // pass read as zeros (offset beyond the buffer)
-  const __amdgpu_buffer_rsrc_t ars = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t*>(p.A), 0, p.act_rows * p.lda * 2, kRsrcWord3);
-  constexpr int kOutOfRange = 0x7FFFFFF0;
-  int a_voff[AJ];
-#pragma unroll
-  for (int j = 0; j < AJ; ++j) {
-    const int e = tid + 256 * j;
-    const int gr = row0 + (e >> 2);
-    const int src = gr < row_count ? (LM ? dp->lm_src[gr] : gr) : 0;
-    a_voff[j] = (e < AE && gr < row_count) ? src * 64 + (e & 3) * 16 : kOutOfRange;
-  }
-
-  // Software pipeline over the k-blocks.  k-block k's weights are loaded into
-  // a register ring D = 4 k-blocks ahead; its A rows are loaded into registers
-  // 6 k-blocks ahead, written to LDS (one of two buffers) 2 ahead and read
-  // into fragment registers 1 ahead, so each iteration's MFMAs wait on
-  // nothing issued in the last few iterations: iteration it reads A(it + 1)'s
-  // fragments and writes A(it + 2) to LDS, multiplies k-block it, then
-  // requests A(it + 6) and W(it + 4).  One barrier per k-block separates an
-  // LDS buffer's writes from its reads.  Indices past the range are clamped
-  // (cache hits, never multiplied), so every iteration issues the same loads
-  // on every path, in the same order (the compiler's waits then hold the
-  // intended depth).
-  constexpr int D = 4, DA = 4;   // weight ring, A register ring (A is requested 6 k-blocks ahead)
-  static_assert(D % DA == 0 && DA % 2 == 0, "one unrolled turn of the weight ring turns the others whole");
-  u32x4 wr[D][NS], ar[DA][AJ], av[2][MB];
-  auto issue_a = [&](int slot, int it) {
-    const int kb = kb0 + min(it, n_kb - 1);
-#pragma unroll
-    for (int j = 0; j < AJ; ++j)
-      ar[slot][j] = __builtin_amdgcn_raw_buffer_load_b128(ars, a_voff[j], kb * (p.act_rows * 64), 0);
-  };
-  // LDS holds row r's 16-byte chunk c at r * 4 + (c ^ ((r >> 1) & 3)): a
-  // fragment read (lanes 0-15 take rows 0-15 of one chunk) then touches
-  // eight different 16-byte bank groups per eight lanes instead of two
-  auto swz = [](int e) { return (e & ~3) | ((e & 3) ^ ((e >> 3) & 3)); };
-  auto put_a = [&](int slot, int buf) {
-#pragma unroll
-    for (int j = 0; j < AJ; ++j) a_lds[buf][swz(tid + 256 * j)] = ar[slot][j];
-  };
-  auto read_a = [&](int slot, int buf) {
-#pragma unroll
-    for (int mt = 0; mt < MB; ++mt) av[slot][mt] = a_lds[buf][swz((mt * 16 + (lane & 15)) * 4 + (lane >> 4))];
-  };
-
-  RowsAcc acc;
-#pragma unroll
-  for (int mt = 0; mt < MB; ++mt)
-#pragma unroll
-    for (int s = 0; s < NS; ++s) acc[mt][s] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  // one strip's MFMAs (row tiles past the pass multiply zeros: no branches
-  // between the fragment reads and the MFMAs)
-  auto mma_strip = [&](int wslot, int aslot, int s) {
-#pragma unroll
-    for (int mt = 0; mt < MB; ++mt)
-      acc[mt][s] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, av[aslot][mt]),
-                                                          __builtin_bit_cast(f16x8, wr[wslot][s]), acc[mt][s], 0, 0, 0);
-  };
-  auto issue_w_strip = [&](int slot, int it, int s) {
-    const int kb = kb0 + min(it, n_kb - 1);
-    wr[slot][s] = __builtin_amdgcn_raw_buffer_load_b128(wrs, w_voff, (kb * p.n_strips + s) * 1024, kCachePolicyNT);
-  };
-  // the A fragments of row tiles [m0, m1)
-  auto read_a_part = [&](int slot, int buf, int m0, int m1) {
-#pragma unroll
-    for (int mt = m0; mt < m1; ++mt) av[slot][mt] = a_lds[buf][swz((mt * 16 + (lane & 15)) * 4 + (lane >> 4))];
-  };
-
-  if (n_kb > 0) {
-    // A(0) and A(1) into LDS, then the loads of the four turns before the
-    // first in the loop's order (W(k + 4) strip 0, A(k + 6), W(k + 4) strips
-    // 1-3, for k = -4 .. -1), so the waits the compiler places at the loop's
-    // top match every turn's
-    issue_a(0, 0);
-    issue_a(1, 1);
-    __builtin_amdgcn_sched_barrier(0);
-    put_a(0, 0);
-    put_a(1, 1);
-#pragma unroll
-    for (int k = -D; k < 0; ++k) {
-#pragma unroll
-      for (int s2 = 0; s2 < NS; ++s2) {
-        __builtin_amdgcn_sched_barrier(0);
-        if (s2 == 1 && k >= -4) issue_a((k + 6) % DA, k + 6);   // A(2) .. A(5)
-        issue_w_strip(k + D, k + D, s2);
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    __syncthreads();
-    read_a(0, 0);
-    __syncthreads();                                 // buffer 0 is free again
-    // One wavefront issues its loads and LDS operations in order with its
-    // MFMAs, so they are interleaved: after each strip's MFMAs go that strip's
-    // next weight load (its registers are free then) and a share of the
-    // fragment reads of A(it + 1); A(it + 2) goes to LDS after the first strip
-    // and A(it + 6) is requested after the second.  The issue cost of the
-    // loads and LDS operations then hides under the MFMAs in flight (issued
-    // as blocks they measured ~650 cycles per k-block against ~650 of MFMA).
-    const int n_it = (n_kb + D - 1) / D * D;
-    for (int it0 = 0; it0 < n_it; it0 += D) {
-#pragma unroll
-      for (int d = 0; d < D; ++d) {
-        const int it = it0 + d;
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-          if (it < n_kb) mma_strip(d, d & 1, s);     // uniform
-          __builtin_amdgcn_sched_barrier(0);
-          if (s == 1) issue_a((d + 2) % DA, it + 6);
-          issue_w_strip(d, it + D, s);
-          __builtin_amdgcn_sched_barrier(0);
-          // A(it + 1): written before the last barrier; row tiles 3s .. 3s + 2
-          read_a_part((d + 1) & 1, (d + 1) & 1, min(3 * s, MB), min(3 * s + 3, MB));
-          if (s == 0) put_a((d + 2) % DA, d & 1);    // A(it + 2) into A(it)'s buffer
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        __syncthreads();
-      }
-    }
-  }
-
-  if (p.ksplit > 1) {
-    // partial tile of this split, in register order (coalesced)
-    float* part = p.part + ((size_t)(tile * p.m_blocks + mb) * p.ksplit + ks) * kRowsPartFloats;
-    static_for<0, MB>([&](auto mtc) __attribute__((always_inline)) {
-      constexpr int mt = decltype(mtc)::value;
-      if (mt >= mt_live) return;                     // uniform
-#pragma unroll
-      for (int s = 0; s < NS; ++s)
-        *reinterpret_cast<f32x4*>(part + (((wave * MB + mt) * NS + s) * 64 + lane) * 4) = acc[mt][s];
-    });
-    return;
-  }
-  if constexpr (EPI != EPI_RESID) {
-    rows_scales<LM>(p, dp, row0, row_count, rs_s);
-    __syncthreads();
-  }
-  rows_epilogue<EPI>(p, dp, acc, tile, row0, row_count, 0, mt_live, wave, lane, rs_s,
-                    EPI == EPI_SWIGLU ? o_lds + wave * MB * 64 : nullptr);
-}
-
-// Sum of the input splits of k_gemm_rows in split order, then the epilogue.
-// One workgroup per 16-row tile of a row block (wavefront w takes GEMM
-// wavefront w's columns); each thread has the loads of up to 8 splits in
-// flight at a time.
-template <int EPI>
-__global__ __launch_bounds__(256) void k_gemm_rows_red(const GemmArgs p) {
-  constexpr int MB = kRowTiles, NS = kRowsWaveStrips;
-  constexpr bool LM = EPI == EPI_LOGITS;
-  __shared__ float rs_s[MB * 16];
-  const int mt_sel = blockIdx.x % MB;
-  const int tile = blockIdx.x / (MB * p.m_blocks), mb = (blockIdx.x / MB) % p.m_blocks;
-  const FwdDesc* dp = p.desc;
-  const int row_count = LM ? dp->n_lm : dp->n_rows;
-  const int row0 = mb * MB * 16;
-  if (row0 + mt_sel * 16 >= row_count) return;      // uniform
-  const int mt_live = min(MB, (row_count - row0 + 15) / 16);
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  if constexpr (EPI != EPI_RESID) rows_scales<LM>(p, dp, row0, row_count, rs_s, mt_sel);
-  const float* base = p.part + (size_t)(tile * p.m_blocks + mb) * p.ksplit * kRowsPartFloats +
-                      (size_t)(((wave * MB + mt_sel) * NS) * 64 + lane) * 4;
-  f32x4 sum[NS];
-#pragma unroll
-  for (int s = 0; s < NS; ++s) sum[s] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < p.ksplit; k0 += 8) {
-    f32x4 v[8][NS];
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-#pragma unroll
-      for (int s = 0; s < NS; ++s)
-        v[u][s] = k0 + u < p.ksplit ? *reinterpret_cast<const f32x4*>(base + (size_t)(k0 + u) * kRowsPartFloats + s * 256)
-                                    : f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-#pragma unroll
-      for (int s = 0; s < NS; ++s)
-        if (k0 + u < p.ksplit) sum[s] += v[u][s];
-  }
-  RowsAcc acc;
-  static_for<0, MB>([&](auto mtc) __attribute__((always_inline)) {
-    constexpr int mt = decltype(mtc)::value;
-#pragma unroll
-    for (int s = 0; s < NS; ++s) acc[mt][s] = mt == mt_sel ? sum[s] : f32x4{0.f, 0.f, 0.f, 0.f};
-  });
-  if constexpr (EPI != EPI_RESID) __syncthreads();
-  rows_epilogue<EPI>(p, dp, acc, tile, row0, row_count, mt_sel, min(mt_live, mt_sel + 1), wave, lane, rs_s);
-}
-
-template <int EPI>
-hipError_t launch_rows(const GemmArgs& a, hipStream_t st, LaunchEvents ev) {
-  const int grid = a.n_tiles * a.m_blocks * a.ksplit;
-  if (ev.start) {
-    hipExtLaunchKernelGGL(k_gemm_rows<EPI>, dim3(grid), dim3(256), 0u, st, ev.start, a.ksplit > 1 ? nullptr : ev.stop,
-                          0u, a);
-  } else {
-    k_gemm_rows<EPI><<<grid, 256, 0, st>>>(a);
-  }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || a.ksplit == 1) return e;
-  if (ev.start) {
-    hipExtLaunchKernelGGL(k_gemm_rows_red<EPI>, dim3(a.n_tiles * a.m_blocks * kRowTiles), dim3(256), 0u, st, nullptr, ev.stop,
-                          0u, a);
-  } else {
-    k_gemm_rows_red<EPI><<<a.n_tiles * a.m_blocks * kRowTiles, 256, 0, st>>>(a);
-  }
-  return hipGetLastError();
-}
-
 template <int EPI, int MT, int S>
 hipError_t launch_one(int nw, const GemmArgs& a, hipStream_t st, LaunchEvents ev) {
   const size_t lds = (size_t)nw * S * MT * 256 * sizeof(float);
@@ -2266,20 +1728,6 @@ hipError_t launch_gemm(int epi, int mt, int S, int nw, const GemmArgs& a, hipStr
     case EPI_RESID: return launch_mt<EPI_RESID>(mt, S, nw, a, st, ev);
     case EPI_SWIGLU: return launch_mt<EPI_SWIGLU>(mt, S, nw, a, st, ev);
     case EPI_LOGITS: return launch_mt<EPI_LOGITS>(mt, S, nw, a, st, ev);
-  }
-  return hipErrorInvalidValue;
-}
-
-hipError_t launch_gemm_rows(int epi, const GemmArgs& a, hipStream_t st, LaunchEvents ev) {
-  if (a.n_tiles < 1 || a.m_blocks < 1 || a.ksplit < 1 || a.ksplit > a.kb_total) return hipErrorInvalidValue;
-  if (a.n_tiles * kRowsTileStrips < a.n_strips || (a.ksplit > 1 && !a.part)) return hipErrorInvalidValue;
-  if ((size_t)a.n_tiles * a.m_blocks * a.ksplit >= (1u << 31)) return hipErrorInvalidValue;
-  if (a.m_blocks * kRowTiles * 16 > kMaxPassRows + kRowTiles * 16) return hipErrorInvalidValue;
-  switch (epi) {
-    case EPI_QKV: return launch_rows<EPI_QKV>(a, st, ev);
-    case EPI_RESID: return launch_rows<EPI_RESID>(a, st, ev);
-    case EPI_SWIGLU: return launch_rows<EPI_SWIGLU>(a, st, ev);
-    case EPI_LOGITS: return launch_rows<EPI_LOGITS>(a, st, ev);
   }
   return hipErrorInvalidValue;
 }

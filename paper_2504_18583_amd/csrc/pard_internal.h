@@ -41,13 +41,8 @@ constexpr int kMaxRows = 64;          // rows of a pass served by the skinny GEM
 constexpr int kMaxPassRows = 512;     // rows of one forward pass over all of its sequences
 constexpr int kMaxPassSeqs = 64;      // sequences in one pass
 constexpr int kMaxLmRows = kMaxPassRows;
-// row-block GEMM: a workgroup of kRowsWaves wavefronts computes kRowTiles*16
-// rows x kRowsWaves*kRowsWaveStrips strips of 16 columns
-constexpr int kRowTiles = 9;
-constexpr int kRowsWaves = 4;
-constexpr int kRowsWaveStrips = 4;
-constexpr int kRowsTileStrips = kRowsWaves * kRowsWaveStrips;
-constexpr int kRowsPartFloats = kRowsWaves * kRowTiles * kRowsWaveStrips * 256;   // one partial tile
+constexpr int kMaxPrefillRows = 4096; // rows of one prefill chunk (a linear pass)
+constexpr size_t kRowsPartTotal = (size_t)18 << 20;   // fp32 partial tiles of split row-block GEMMs (72 MiB)
 constexpr int kBlock = 256;
 // skinny GEMM with a split input dimension: tile counters and fp32 partial tiles
 constexpr int kSplitCounters = 4096;
@@ -63,8 +58,8 @@ constexpr int kAttnRecords = 512;  // max (query group, key chunk) partial recor
 
 // Position of activation element (row, k) in a k-blocked buffer with `slots`
 // row slots per 32-column block: kMaxRows for passes served by the skinny
-// GEMM (so a decode pass's few rows stay close together), kMaxPassRows for the
-// row-block GEMM's passes.
+// GEMM (so a decode pass's few rows stay close together), kMaxPassRows or the
+// engine's prefill rows for the row-block GEMM's passes.
 __host__ __device__ inline size_t act_index(int row, int k, int slots) {
   return ((size_t)(k >> 5) * slots + row) * 32 + (k & 31);
 }
@@ -130,14 +125,17 @@ struct PassSeq {
 
 // Rows of the next forward pass of one model: one or several sequences, each
 // a contiguous run of rows.  Written by the host (granular calls, prefill) or
-// by the step tail of the previous pass (fused loop).
+// by the step tail of the previous pass (fused loop).  A linear pass (prefill
+// chunks of more than kMaxRows rows) is one sequence's consecutive positions:
+// row r is at seq[0].pos0 + r, its token ids are in a buffer of their own
+// (k_embed), and ids / pos / slot are not filled.
 struct FwdDesc {
   int n_rows;                  // rows in the pass
   int n_seq;                   // sequences in the pass
   int n_lm;                    // rows fed to the lm_head
-  int pad;
+  int linear;                  // 1: a linear pass
   PassSeq seq[kMaxPassSeqs];
-  int ids[kMaxPassRows];       // token id of each row
+  int ids[kMaxPassRows];       // token id of each row (not in a linear pass, as the next two)
   int pos[kMaxPassRows];       // absolute position of each row
   int slot[kMaxPassRows];      // sequence slot of each row
   int lm_src[kMaxPassRows];    // pass row of each lm row
@@ -326,7 +324,17 @@ struct CodArgs {
 // Launchers (return hipSuccess or the launch error).
 hipError_t launch_gemm(int epi, int mt, int S, int nw, const GemmArgs& a, hipStream_t st,
                        LaunchEvents ev = LaunchEvents{});
-hipError_t launch_gemm_rows(int epi, const GemmArgs& a, hipStream_t st, LaunchEvents ev = LaunchEvents{});
+// Row-block GEMM plan (passes of more than kMaxRows rows): tile variant, grid
+// and input split for a weight of n_strips x kb_total blocks, best at typ_rows
+// rows and covering max_rows.  A row's sums of squares (EPI_RESID) and argmax
+// entries (EPI_LOGITS) come in `entries` pieces of ent_strips strips each.
+struct RowsPlan {
+  int variant = -1, n_tiles = 0, m_blocks = 0, ksplit = 1;
+  int ent_strips = 4, entries = 0;
+};
+RowsPlan plan_rows(int n_strips, int kb_total, int max_rows, int typ_rows);
+hipError_t launch_gemm_rows(int epi, int variant, const GemmArgs& a, hipStream_t st,
+                            LaunchEvents ev = LaunchEvents{});
 // QKV GEMM (mt row tiles, S strips per workgroup, one input range) and the
 // single-chunk decode attention reading its output, in one launch; only when
 // every workgroup of it is co-resident (qkv_attn_capacity: workgroups the
