@@ -27,9 +27,9 @@ LAYER_EXE = os.path.join(PKG, "layer_counters")
 STEP_EXE = os.path.join(PKG, "step_counters")
 MFMA_EXE = os.path.join(PKG, "mfma_peak")
 
-SOURCES = ["engine.hip", "gemm.hip", "gemm_rows.hip", "attention.hip", "device_init.hip", "cod.hip",
+SOURCES = ["engine.hip", "gemm.hip", "gemm_rows.hip", "attention.hip", "attn_prefill.hip", "device_init.hip", "cod.hip",
            "gemm_counters.hip", "layer_counters.hip", "step_counters.hip", "mfma_peak.hip"]
-LIB_SOURCES = SOURCES[:6]
+LIB_SOURCES = SOURCES[:7]
 
 HIPCC = os.environ.get("HIPCC", shutil.which("hipcc") or "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

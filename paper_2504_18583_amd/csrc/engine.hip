@@ -658,7 +658,11 @@ pard_status forward(pard_ctx* c, int w, const PassSpec& ps) {
   const bool wide = !rows && l_bound <= kAttnWideMaxKeys;
   int nqt = std::min(attn_max_q_tiles(s.head_dim), ceil_div(qpairs, 16));
   if (wide) nqt = std::min(nqt, s.head_dim == 128 ? 1 : kAttnWideQTiles64);
-  const int n_qblocks = ceil_div(qpairs, 16 * nqt);
+  // prefill chunks: the kernel that shares the keys among the wavefronts
+  const int pre_nqt = rows && ps.n_seq == 1
+                          ? attn_prefill_tiles(s.head_dim, s.n_kv_heads, qpairs, ps.max_rows, l_bound) : 0;
+  const int n_qblocks = pre_nqt ? ceil_div(qpairs, 64 * pre_nqt) : ceil_div(qpairs, 16 * nqt);
+  if (pre_nqt) nqt = pre_nqt;
   int split_len = wide ? ceil_div(l_bound, 128) * 128 : kAttnChunk;
   // row-block passes over several sequences (batched decode): 1024-key
   // chunks (batch-32 step 15.5 ms with 256, 15.4 with 512, 15.2 with 1024;
@@ -674,7 +678,7 @@ pard_status forward(pard_ctx* c, int w, const PassSpec& ps) {
   }
   // (one chunk writes no records)
   while (split_len < l_bound && (int64_t)ps.n_seq * n_qblocks * ceil_div(l_bound, split_len) > kAttnRecords) split_len *= 2;
-  const int n_splits = ceil_div(l_bound, split_len);
+  const int n_splits = pre_nqt ? 1 : ceil_div(l_bound, split_len);
   // decode passes over one attention chunk: QKV GEMM and attention in one
   // launch when its grid fits the device at once
   const int mt_q = ceil_div(ps.max_rows, 16);
@@ -802,7 +806,7 @@ pard_status forward(pard_ctx* c, int w, const PassSpec& ps) {
     }
     if (!fused) {  // attention
       Timed t(c, cls0 + 2);
-      HIP_TRY(c, launch_attention(s.head_dim, aa, c->stream));
+      HIP_TRY(c, pre_nqt ? launch_attn_prefill(s.head_dim, aa, c->stream) : launch_attention(s.head_dim, aa, c->stream));
     }
     if (!fused_o) {  // O-projection + residual
       HIP_TRY(c, run_gemm(c, cls0 + 3, EPI_RESID, ps.max_rows, r_o, o_args(M, L, act_rows), M.p_o));

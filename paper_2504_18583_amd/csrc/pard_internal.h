@@ -357,6 +357,11 @@ hipError_t launch_qkv_attn(int mt, int S, int head_dim, const GemmArgs& g, const
 hipError_t launch_tail(const TailArgs& a, int n_seq, hipStream_t st);
 hipError_t launch_stage(const TailArgs& a, hipStream_t st);
 hipError_t launch_attention(int head_dim, const AttnArgs& a, hipStream_t st);
+// Attention of a prefill chunk (one sequence, n_splits = 1): nqt =
+// attn_prefill_tiles (0: use launch_attention), 64*nqt query pairs per
+// workgroup.
+int attn_prefill_tiles(int head_dim, int n_kv, int qpairs, int rows, int l_bound);
+hipError_t launch_attn_prefill(int head_dim, const AttnArgs& a, hipStream_t st);
 size_t attn_part_floats(int head_dim, int nqt);
 int attn_max_q_tiles(int head_dim);
 hipError_t launch_cod(const int32_t* tokens, const int64_t* tok_off, const int64_t* out_off, int n_samples,

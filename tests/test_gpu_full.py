@@ -290,3 +290,34 @@ def test_long_key_chunks_lockstep(B, heads, hd, ctx, chunk):
         say(f"    max |logit err| {worst:.3g}")
     finally:
         eng.close()
+
+
+@pytest.mark.parametrize("heads,kv,hd,n", [
+    (8, 2, 128, 65),     # 16 rows per workgroup: one row in the last
+    (8, 2, 128, 80),     # whole workgroups
+    (4, 4, 128, 129),    # one head per KV head: 64 rows per workgroup; one key in the last stage
+    (7, 1, 64, 66),      # rows split between workgroups
+    (8, 2, 64, 191),     # keys end inside a stage
+    (14, 2, 128, 500),
+    (32, 8, 128, 3100),  # two query tiles per wavefront
+    (32, 8, 128, 4300),  # two chunks: the second one's keys mostly precede it
+])
+def test_prefill_attention_tiles_lockstep(B, heads, kv, hd, n):
+    """Prefill chunks' attention at the edges of its tiles (64 or 128 query
+    pairs per workgroup, 64 keys per stage).  With two layers every row's
+    attention reaches the last row's logits and the steps after it."""
+    from gpu_common import Lockstep
+    wl = pi.WORKLOADS["tiny"]
+    t_spec = replace(pi.with_dtype(wl.target, "bf16"), n_layers=2, n_heads=heads, n_kv_heads=kv, head_dim=hd)
+    d_spec = replace(pi.with_dtype(wl.draft, "bf16"), n_heads=heads, n_kv_heads=kv, head_dim=hd)
+    prompt = [int(x) for x in pi.gen_prompt(29, t_spec.vocab, n)]
+    say(f"[gpu] prefill attention {heads}/{kv} heads of {hd}, {n} rows")
+    target, draft = oracle.build_model(t_spec), oracle.build_model(d_spec)
+    eng = B.Engine(t_spec, d_spec, wl.mask_id, max_ctx=n + 64, max_k=4)
+    try:
+        ls = Lockstep(eng, target, draft, prompt, 4, wl.mask_id, tag=f"prefill {heads}/{kv}x{hd} {n}")
+        ls.prefill(cache_only_prefix=True)
+        ls.step()
+        say(f"    max |logit err| {ls.worst:.3g}")
+    finally:
+        eng.close()
