@@ -23,7 +23,7 @@ namespace {
 
 constexpr int kDescRing = 128;
 constexpr int kStepsPerPlan = 32;            // fused steps between two host checks of the length class
-constexpr int kLmStrips = 8;                 // strips per lm_head workgroup at up to 16 lm rows
+constexpr int kLmStrips = 8;                 // strips per lm_head workgroup at up to 48 lm rows
 constexpr int kGatherMax = 4096;
 static_assert(kRowsPartTotal >= kSplitPartFloats, "split partial tiles share the row-block buffer");
 
@@ -53,23 +53,30 @@ struct Bump {
 };
 
 // Tile plan of one skinny GEMM: S strips per workgroup, nw wavefronts splitting
-// the input dimension.  nw depends only on the weight shape (for the row
-// counts of decode passes), so per-element summation order does not depend on
-// how many rows a pass has.
+// the input dimension.  nw depends only on the weight shape and on whether the
+// pass has more than 16 rows, and so does the order of a sum.
 struct GemmPlan {
   int n_strips = 0, kb_total = 0;
   int nw = 4;   // one wavefront per SIMD: more waves per workgroup measured slower at every decode shape
+  int nw_mid = 4;   // the same for passes of 17 rows and more
   int ksplit = 1;   // input ranges of the skinny GEMM
 };
 
 int pick_S(int epi, int n_strips, int mt) {
-  if (epi == EPI_RESID) {
-    // residual GEMMs also write the per-tile row sums that the next
-    // normalised GEMM adds up, so their tile count must not depend on the
-    // pass: one strip per workgroup up to 256 strips (one round), two beyond
-    return (n_strips > 256 && n_strips % 2 == 0) ? 2 : 1;
+  // residual GEMMs: one strip per workgroup up to 256 strips (one round), two
+  // beyond (a tile is also one entry of the row sums that the next normalised
+  // GEMM adds up: resid_ss_tiles)
+  if (epi == EPI_RESID) return (n_strips > 256 && n_strips % 2 == 0) ? 2 : 1;
+  // lm_head: eight strips per workgroup (four at 49 rows and more), fewer for
+  // small vocabularies until the workgroups cover the CUs (41 rows, 4096-wide
+  // hidden: 8016 strips 242 us at 2 per workgroup, 202 at 4, 194 at 8; 57 rows
+  // 264, 220, 228; 256 strips, 41 rows: 16.1 at 2, 13.4 at 1)
+  if (epi == EPI_LOGITS) {
+    int s = mt <= 3 ? kLmStrips : 4;
+    while (s > 1 && (n_strips % s || n_strips / s < 256)) s >>= 1;
+    return s;
   }
-  if (mt == 1 && epi != EPI_LOGITS) {
+  if (mt == 1) {
     // decode rows: the fewest strips per workgroup that cover the weight in
     // one round of at most 256 workgroups (one per CU), so each CU reads the
     // activation rows once; from 8 strips on the last workgroup may hold
@@ -103,12 +110,19 @@ int pick_S(int epi, int n_strips, int mt) {
     }
     return best;
   }
+  // 17 to 64 rows: the activations a workgroup reads (1 KiB per row tile and
+  // k-block, against S KiB of weights) come from the XCD's L2, so wider tiles
+  // read less of them; one round of workgroups where that is possible.  Measured
+  // (us at 41 rows, rotating weight copies): gate/up 8B 1792 strips 56 at 2, 44
+  // at 4, 41 at 7; 1B 1024 strips 17.9 at 2, 16.3 at 4, 23.6 at 8; Qwen2.5-7B
+  // 2368 strips 65 at 2, 55 at 4, 70 at 8; QKV 8B 384 strips 21.4 at 1, 18.2 at 2,
+  // Qwen2.5-7B 288 strips 18.6 and 15.7, 1B 192 strips 9.2 and 11.8.
   int s = 1;
-  // two strips share one activation stream once that still leaves >= 192
-  // workgroups
-  if (epi == EPI_QKV && n_strips >= 384) s = 2;
-  if (epi == EPI_SWIGLU) s = 2;
-  if (epi == EPI_LOGITS) s = (mt == 1) ? kLmStrips : 2;
+  if (epi == EPI_QKV && n_strips > 256) s = 2;
+  if (epi == EPI_SWIGLU) {
+    s = n_strips >= 512 ? 4 : 2;
+    if (n_strips > 1024 && n_strips <= 1792 && n_strips % 7 == 0) return 7;
+  }
   while (s > 1 && n_strips % s) s >>= 1;
   return s;
 }
@@ -125,16 +139,25 @@ GemmPlan plan_gemm(int epi, int n_pad, int k_pad) {
   return p;
 }
 
-// Wavefronts per workgroup for a pass of mt row tiles (LDS <= 32 KiB).
-int plan_nw(const GemmPlan& p, int S, int mt) {
-  int nw = p.nw;
-  while (nw > 4 && nw * S * mt > 32) nw >>= 1;
-  return nw;
+// Wavefronts per workgroup for a pass of mt row tiles.
+int plan_nw(const GemmPlan& p, int mt) { return mt == 1 ? p.nw : p.nw_mid; }
+
+// Strips per workgroup and input ranges of a residual GEMM for a pass of mt row
+// tiles.  A long weight of at most 256 strips takes two strips per workgroup
+// over two input ranges from 17 rows on: half the activation reads in the same
+// number of workgroups, for about 2.5 us of partial-tile exchange (us at 25 and
+// 57 rows: 8B down, 448 k-blocks, 27.3 -> 26.1 and 39.4 -> 34.4; Qwen2.5-7B down,
+// 592 k-blocks, 35.2 -> 32.1 and 50.3 -> 41.8; 8B O, 128 k-blocks, 10.6 -> 13.2).
+struct ResidPlan { int S, ksplit; };
+ResidPlan resid_plan(const GemmPlan& p, int mt) {
+  if (mt > 1 && p.ksplit == 1 && p.n_strips > 128 && p.n_strips <= 256 && p.n_strips % 2 == 0 && p.kb_total >= 384)
+    return {2, 2};
+  return {pick_S(EPI_RESID, p.n_strips, mt), p.ksplit};
 }
 
 // Tiles that write row sums of squares per residual GEMM of a pass served by
 // the skinny GEMM (its consumers' ss_tiles).
-int resid_ss_tiles(const GemmPlan& p) { return p.n_strips / pick_S(EPI_RESID, p.n_strips, 1); }
+int resid_ss_tiles(const GemmPlan& p, int mt) { return p.n_strips / resid_plan(p, mt).S; }
 
 struct Layer {
   uint16_t *wqkv = nullptr, *wo = nullptr, *wgu = nullptr, *wd = nullptr;
@@ -312,17 +335,20 @@ void derive(ModelDev& M, const pard_model_spec& s, int max_ctx) {
   M.group = s.n_heads / s.n_kv_heads;
   M.p_qkv = plan_gemm(EPI_QKV, M.nqkv, M.d);
   M.p_o = plan_gemm(EPI_RESID, M.d, M.q_dim);
-  // one strip per workgroup: eight wavefronts over the input (at every row
-  // tile count), as the O units fused into the QKV + attention launch use,
-  // so a row's O-projection is summed in the same order whether or not its
-  // pass runs fused (the unfused launch measured 8.3 -> 10.9 us at the 8B
-  // shape for it; 16k-context 8B/1B step 4.53 -> 4.57 ms)
+  // one strip per workgroup: eight wavefronts over the input at one row tile,
+  // as the O units fused into the QKV + attention launch use, so a row's
+  // O-projection is summed in the same order whether or not its decode pass
+  // runs fused (the unfused launch measured 8.3 -> 10.9 us at the 8B shape for
+  // it; 16k-context 8B/1B step 4.53 -> 4.57 ms).  More row tiles have no fused O
+  // and keep four (25 rows, 8B: 10.6 against 13.1 us)
   if (pick_S(EPI_RESID, M.p_o.n_strips, 1) == 1) M.p_o.nw = 8;
+  // (QKV at 41 rows: 8B 18.2 us with four wavefronts, 17.6 with eight; 1B 9.2, 8.7)
+  M.p_qkv.nw_mid = 8;
   M.p_gu = plan_gemm(EPI_SWIGLU, 2 * M.f_pad, M.d);
   M.p_d = plan_gemm(EPI_RESID, M.d, M.f_pad);
   M.p_lm = plan_gemm(EPI_LOGITS, s.vocab, M.d);
   // (the row-block GEMM's tiles are at least two strips wide)
-  M.ss_tiles_max = std::max(resid_ss_tiles(M.p_o), ceil_div(M.p_o.n_strips, 2));
+  M.ss_tiles_max = std::max(resid_ss_tiles(M.p_o, 1), ceil_div(M.p_o.n_strips, 2));
 }
 
 // Lays out (base == nullptr: sizes) every device region of a context.
@@ -603,13 +629,18 @@ hipError_t run_gemm(pard_ctx* c, int cls, int epi, int max_rows, const RowsPlan&
     return launch_gemm_rows(epi, r.variant, a, c->stream, ev);
   }
   const int mt = ceil_div(max_rows, 16);
-  const int S = pick_S(epi, p.n_strips, mt);
-  a.n_tiles = ceil_div(p.n_strips, S);
+  int S = pick_S(epi, p.n_strips, mt);
   a.ksplit = p.ksplit;
-  a.kb_split = ceil_div(p.kb_total, p.ksplit);
+  if (epi == EPI_RESID) {
+    const ResidPlan rp = resid_plan(p, mt);
+    S = rp.S;
+    a.ksplit = rp.ksplit;
+  }
+  a.n_tiles = ceil_div(p.n_strips, S);
+  a.kb_split = ceil_div(p.kb_total, a.ksplit);
   a.part = c->rows_part;
   a.counters = c->split_counters;
-  return launch_gemm(epi, mt, S, plan_nw(p, S, mt), a, c->stream, ev);
+  return launch_gemm(epi, mt, S, plan_nw(p, mt), a, c->stream, ev);
 }
 
 pard_status forward(pard_ctx* c, int w, const PassSpec& ps) {
@@ -622,7 +653,8 @@ pard_status forward(pard_ctx* c, int w, const PassSpec& ps) {
   // row-block plans of the pass's GEMMs; the row sums of squares of the
   // residual GEMMs come in their plan's pieces
   RowsPlan r_qkv, r_o, r_gu, r_d;
-  int ss_o = resid_ss_tiles(M.p_o), ss_d = resid_ss_tiles(M.p_d);
+  const int mt_pass = ceil_div(ps.max_rows, 16);
+  int ss_o = resid_ss_tiles(M.p_o, mt_pass), ss_d = resid_ss_tiles(M.p_d, mt_pass);
   if (rows) {
     auto plan = [&](const GemmPlan& p) { return plan_rows(p.n_strips, p.kb_total, ps.max_rows, typ); };
     r_qkv = plan(M.p_qkv);
@@ -709,13 +741,13 @@ pard_status forward(pard_ctx* c, int w, const PassSpec& ps) {
   const int S_gu = pick_S(EPI_SWIGLU, M.p_gu.n_strips, 1);
   bool fused_gu = false, fused_d = false;
   if (fused_o && c->use_fused_gu && (S_gu == 4 || S_gu == 7) && M.p_gu.ksplit == 1 &&
-      M.p_gu.n_strips % S_gu == 0 && plan_nw(M.p_gu, S_gu, 1) == 4) {
+      M.p_gu.n_strips % S_gu == 0 && plan_nw(M.p_gu, 1) == 4) {
     const int n_qkv = M.p_qkv.n_strips / S_q;
     const int gu_tiles = M.p_gu.n_strips / S_gu;
     // and the down projection (one strip per tile, one input range), whose
     // workgroups wait for every gate/up tile
     const int d_S = c->use_fused_d && M.p_d.ksplit <= 2 && pick_S(EPI_RESID, M.p_d.n_strips, 1) == 1 &&
-                    plan_nw(M.p_d, 1, 1) == 4 ? 1 : 0;
+                    plan_nw(M.p_d, 1) == 4 ? 1 : 0;
     const int d_units = d_S ? M.p_d.n_strips * M.p_d.ksplit : 0;
     const int pre_max = std::min(qkv_attn_gu_pre_max(S_q, s.head_dim, M.p_o.kb_total, S_gu, d_S), M.p_gu.kb_total / 4);
     const int pre = c->gu_pre >= 0 ? std::min(c->gu_pre, pre_max) : pre_max;

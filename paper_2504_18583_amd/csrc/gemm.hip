@@ -15,9 +15,8 @@
 // encoding) feed v_mfma_f32_16x16x32_f16 directly.
 //
 // The wavefront partials are summed in LDS in wave order, so results are
-// deterministic; the split depends only on the weight shape, so a row's result
-// does not depend on how many other rows are in the pass.  No workgroup ever
-// waits for another one.
+// deterministic; the split depends only on the weight shape and on whether the
+// pass has more than 16 rows.  No workgroup ever waits for another one.
 //
 // Shapes with few strips also split the input dimension over the grid's y
 // dimension (P contiguous ranges of k-blocks), so that narrow GEMMs still
@@ -71,6 +70,10 @@ __device__ __forceinline__ float wave_incl_scan(float v, int lane) {
   return v;
 }
 
+// LDS of a workgroup's wavefront partials (launch_gemm): four wavefronts of 7
+// strips and 4 row tiles.
+constexpr size_t kGemmLdsMax = 112 * 1024;
+
 // Input iterations per wavefront that a fused gate/up tile may take from LDS.
 constexpr int kGuPreMax = 8;
 
@@ -104,7 +107,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, const int tile, con
   constexpr int NE = S * MT * 256;   // elements of one workgroup tile
   constexpr int NJ = S * MT;         // elements per thread in the epilogue (first 256 threads)
   // k-blocks per pipeline stage: 8 KiB of W per wave (smaller for prefill-sized row counts)
-  constexpr int U = MT >= 3 ? 2 : ((8 / S) > 0 ? 8 / S : 1);
+  constexpr int U = MT >= 3 ? (S <= 2 ? 2 : 1) : MT == 2 && S == 1 ? 4 : ((8 / S) > 0 ? 8 / S : 1);
   __shared__ float rs_s[MT * 16];
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -157,29 +160,29 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, const int tile, con
   constexpr bool NORM = EPI != EPI_RESID;             // A is RMS-normalised: rows need 1/rms
 
   // 1/rms per row from the producer's per-tile sums of squares: 16 threads per
-  // row, fixed summation order.  For one row tile the loads of the first 256
-  // tiles are issued ahead of the weight stream (ss_issue) and summed just
-  // before the first MFMAs (ss_finish): loads complete in issue order, so
-  // waiting for them would otherwise also wait for every weight load in
-  // flight and empty the pipeline.
-  float ss_part[16];
-  auto ss_issue = [&](int row) {
+  // row and row tile, fixed summation order.  The loads of the first 256 tiles
+  // are issued ahead of the weight stream (ss_issue) and summed just before
+  // the first MFMAs (ss_finish): loads complete in issue order, so waiting for
+  // them would otherwise also wait for every weight load in flight and empty
+  // the pipeline.
+  float ss_part[MT][16];
+  auto ss_issue = [&](int mt, int row) {
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
       // unconditional loads (a tile index past the end re-reads the last
       // tile and is dropped when summed), so none waits behind a branch
       const int q = (tid & 15) + 16 * u;
       if constexpr (PM)   // written by the O workers of this launch: device scope
-        ss_part[u] = __hip_atomic_load(p.ss_in + (size_t)row * p.ss_stride + min(q, p.ss_tiles - 1), __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
+        ss_part[mt][u] = __hip_atomic_load(p.ss_in + (size_t)row * p.ss_stride + min(q, p.ss_tiles - 1),
+                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       else
-        ss_part[u] = p.ss_in[(size_t)row * p.ss_stride + min(q, p.ss_tiles - 1)];
+        ss_part[mt][u] = p.ss_in[(size_t)row * p.ss_stride + min(q, p.ss_tiles - 1)];
     }
   };
-  auto ss_finish = [&](int row) {
+  auto ss_finish = [&](int mt, int row) {
     float t = 0.f;
 #pragma unroll
-    for (int u = 0; u < 16; ++u) t += (tid & 15) + 16 * u < p.ss_tiles ? ss_part[u] : 0.f;
+    for (int u = 0; u < 16; ++u) t += (tid & 15) + 16 * u < p.ss_tiles ? ss_part[mt][u] : 0.f;
     for (int q0 = (tid & 15) + 256; q0 < p.ss_tiles; q0 += 256) {
       float part[16];
 #pragma unroll
@@ -198,7 +201,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, const int tile, con
     t += __shfl_xor(t, 4);
     t += __shfl_xor(t, 2);
     t += __shfl_xor(t, 1);
-    if ((tid & 15) == 0) rs_s[tid >> 4] = 1.0f / sqrtf(t * p.inv_k + p.eps);
+    if ((tid & 15) == 0) rs_s[mt * 16 + ((tid & 255) >> 4)] = 1.0f / sqrtf(t * p.inv_k + p.eps);
   };
   // thread tid (< 256) of the epilogue owns, for j = s*MT + mt, element
   // (row, col) below; its epilogue operands are fetched while the weights stream
@@ -219,11 +222,19 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, const int tile, con
     e_pos[mt] = EPI == EPI_QKV ? dp->pos[mt * 16 + rsub] : 0;
     e_slot[mt] = EPI == EPI_QKV ? dp->slot[mt * 16 + rsub] : 0;
   }
-  const int lm_ss = LM ? dp->lm_src[(tid & 255) >> 4] : 0;
+  int ss_row[MT];                                     // the row whose sums this thread adds, per row tile
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    const int r = mt * 16 + ((tid & 255) >> 4);
+    ss_row[mt] = LM ? dp->lm_src[r] : r;
+  }
   // rows of a pass's activations need no descriptor (rows past the pass read
   // unused sums and are never stored)
-  if constexpr (NORM && !LM && MT == 1 && !PM) {
-    if (tid < 256) ss_issue(tid >> 4);
+  if constexpr (NORM && !LM && !PM) {
+    if (tid < 256) {
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) ss_issue(mt, ss_row[mt]);
+    }
   }
   __builtin_amdgcn_sched_barrier(0);
 
@@ -244,9 +255,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, const int tile, con
   __builtin_amdgcn_sched_barrier(0);
 
   const int row_count = LM ? dp->n_lm : dp->n_rows;
-  const int ss_row = LM ? ((tid & 255) >> 4 < row_count ? lm_ss : 0) : (tid & 255) >> 4;
-  if constexpr (LM && MT == 1) {
-    if (tid < 256) ss_issue(ss_row);              // lm rows read their source row's sums
+  if constexpr (LM) {                             // lm rows read their source row's sums
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+      if (mt * 16 + ((tid & 255) >> 4) >= row_count) ss_row[mt] = 0;
+    if (tid < 256) {
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) ss_issue(mt, ss_row[mt]);
+    }
   }
 
   // A fragment of this lane: row (lane % 16) of each M tile, 8 columns at
@@ -320,31 +336,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, const int tile, con
     }
   };
 
-  // several row tiles: the same sums, loaded and summed in one go
-  auto row_scales = [&]() {
-    if (tid < 256) {
-      for (int r = tid >> 4; r < MT * 16; r += 16) {
-        const int row = r < row_count ? (LM ? dp->lm_src[r] : r) : 0;
-        float t = 0.f;
-        for (int q0 = tid & 15; q0 < p.ss_tiles; q0 += 256) {
-          float part[16];
-#pragma unroll
-          for (int u = 0; u < 16; ++u) {
-            const int q = q0 + 16 * u;
-            part[u] = q < p.ss_tiles ? p.ss_in[(size_t)row * p.ss_stride + q] : 0.f;
-          }
-#pragma unroll
-          for (int u = 0; u < 16; ++u) t += part[u];
-        }
-        t += __shfl_xor(t, 8);
-        t += __shfl_xor(t, 4);
-        t += __shfl_xor(t, 2);
-        t += __shfl_xor(t, 1);
-        if ((tid & 15) == 0) rs_s[r] = 1.0f / sqrtf(t * p.inv_k + p.eps);
-      }
-    }
-  };
-
   // sched_barrier keeps the compiler from sinking the prefetch next to its use
   if constexpr (PM == 2) {
     int its = 0;
@@ -374,7 +365,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, const int tile, con
     load_w(w1, its + U);                                // the second stage, before the wait
     __builtin_amdgcn_sched_barrier(0);
     attn::fuse_wait_on<kFuseLanes>(fc->counters + 2 * kFuseLanes * kFuseStride, fc->n_odone, fc->err);
-    if (tid < 256) ss_issue(tid >> 4);
+    if (tid < 256) ss_issue(0, ss_row[0]);
     load_a(a0, its);
     load_a(a1, its + U);
     // A of the preloaded iterations (iterations past `pre` re-read the last
@@ -385,7 +376,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, const int tile, con
       ap[i] = __builtin_amdgcn_raw_buffer_load_b128(ars, a_voff[0], (kb0 + wave + min(i, max(pre - 1, 0)) * nw) *
                                                     (p.act_rows * 64), attn::kCachePolicyDevice);
     __builtin_amdgcn_sched_barrier(0);
-    if (tid < 256) ss_finish(ss_row);
+    if (tid < 256) ss_finish(0, ss_row[0]);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < kGuPreMax; ++i) {
@@ -418,13 +409,15 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, const int tile, con
     int its = 0;
     load_a(a0, its);
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (NORM && MT > 1) row_scales();     // overlaps the first weight loads
     load(w1, a1, its + U);
     __builtin_amdgcn_sched_barrier(0);
     prefetch_epilogue();
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (NORM && MT == 1) {
-      if (tid < 256) ss_finish(ss_row);
+    if constexpr (NORM) {
+      if (tid < 256) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) ss_finish(mt, ss_row[mt]);
+      }
     }
     __builtin_amdgcn_sched_barrier(0);
     // One exit per pair of stages, at the loop's top: with an exit between
@@ -446,9 +439,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, const int tile, con
     compute(w0, a0, its);
     if (its + U < n_it) compute(w1, a1, its + U);     // uniform
   } else {
-    if constexpr (NORM && MT > 1) row_scales();
-    if constexpr (NORM && MT == 1) {
-      if (tid < 256) ss_finish(ss_row);
+    if constexpr (NORM) {
+      if (tid < 256) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) ss_finish(mt, ss_row[mt]);
+      }
     }
     prefetch_epilogue();
   }
@@ -595,42 +590,32 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& p, const int tile, con
       }
     flag_range(bad, p.ovf);
   } else {  // EPI_LOGITS
-    constexpr int TW = S * 16;
-    __syncthreads();   // everyone is done reading red; it becomes the [row][col] tile
-    if (epi) {
+    // (max, argmax) of a row's S*16 columns: over the strips in registers, then
+    // over the row's 16 lanes with DPP moves
+    if (!epi) return;   // whole wavefronts; no barrier follows in this epilogue
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        const int s = j / MT, mt = j % MT;
-        const int row = mt * 16 + rsub;
-        const int c = s * 16 + csub;
-        const float val = v[j] * rs_s[row];
-        red[row * TW + c] = val;
-        if (row < row_count) p.logits[(size_t)row * p.vocab + tile * TW + c] = val;
-      }
-    }
-    __syncthreads();
-    if (!epi) return;
-    for (int r = ew; r < row_count; r += 4) {
+    for (int mt = 0; mt < MT; ++mt) {
+      const int row = mt * 16 + rsub;
       float bv = -INFINITY;
       int bi = INT_MAX;
-      for (int c = lane; c < TW; c += 64) {
-        const float x = red[r * TW + c];
-        if (better(x, c, bv, bi)) { bv = x; bi = c; }
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        const int n = (tile * S + s) * 16 + csub;
+        const float val = v[s * MT + mt] * rs_s[row];
+        if (row < row_count) p.logits[(size_t)row * p.vocab + n] = val;
+        if (better(val, n, bv, bi)) { bv = val; bi = n; }
       }
-      for (int off = 32; off > 0; off >>= 1) {
-        const float ov = __shfl_xor(bv, off);
-        const int oi = __shfl_xor(bi, off);
-        if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
-      }
-      if (lane == 0) {
-        p.amax_val[(size_t)r * p.amax_stride + tile] = bv;
-        p.amax_idx[(size_t)r * p.amax_stride + tile] = (bi == INT_MAX) ? INT_MAX : tile * TW + bi;
+      best16(bv, bi);
+      if (csub == 0 && row < row_count) {
+        p.amax_val[(size_t)row * p.amax_stride + tile] = bv;
+        p.amax_idx[(size_t)row * p.amax_stride + tile] = bi;
       }
       if (p.samp_k > 0.f) {         // sampling: the tile's softmax weight relative to its max
         float sw = 0.f;
-        for (int c = lane; c < TW; c += 64) sw += __builtin_amdgcn_exp2f((red[r * TW + c] - bv) * p.samp_k);
-        sw = wave_sum(sw);
-        if (lane == 0) p.amax_sum[(size_t)r * p.amax_stride + tile] = sw;
+#pragma unroll
+        for (int s = 0; s < S; ++s) sw += __builtin_amdgcn_exp2f((v[s * MT + mt] * rs_s[row] - bv) * p.samp_k);
+        sw = sum16(sw);
+        if (csub == 0 && row < row_count) p.amax_sum[(size_t)row * p.amax_stride + tile] = sw;
       }
     }
   }
@@ -1457,6 +1442,11 @@ template <int EPI, int MT, int S>
 hipError_t launch_one(int nw, const GemmArgs& a, hipStream_t st, LaunchEvents ev) {
   const size_t lds = (size_t)nw * S * MT * 256 * sizeof(float);
   if (nw > 8) return hipErrorInvalidValue;
+  if (lds > 64 * 1024) {   // (wide tiles of several row tiles: above the default limit)
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm<MT, S, EPI>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
   if (ev.start) {
     hipExtLaunchKernelGGL(k_gemm<MT, S, EPI>, dim3(a.n_tiles, a.ksplit), dim3(64 * nw), (uint32_t)lds, st, ev.start, ev.stop,
                           0u, a);
@@ -1471,9 +1461,9 @@ hipError_t launch_s(int S, int nw, const GemmArgs& a, hipStream_t st, LaunchEven
   switch (S) {
     case 1: return launch_one<EPI, MT, 1>(nw, a, st, ev);
     case 2: return launch_one<EPI, MT, 2>(nw, a, st, ev);
-    case 4: if constexpr (MT <= 2) return launch_one<EPI, MT, 4>(nw, a, st, ev); break;
-    case 7: if constexpr (MT == 1 && EPI == EPI_SWIGLU) return launch_one<EPI, MT, 7>(nw, a, st, ev); break;
-    case 8: if constexpr (MT == 1 && (EPI == EPI_LOGITS || EPI == EPI_SWIGLU)) return launch_one<EPI, MT, 8>(nw, a, st, ev); break;
+    case 4: if constexpr (EPI == EPI_SWIGLU || EPI == EPI_LOGITS) return launch_one<EPI, MT, 4>(nw, a, st, ev); break;
+    case 7: if constexpr (EPI == EPI_SWIGLU) return launch_one<EPI, MT, 7>(nw, a, st, ev); break;
+    case 8: if constexpr ((EPI == EPI_LOGITS && MT <= 3) || (MT == 1 && EPI == EPI_SWIGLU)) return launch_one<EPI, MT, 8>(nw, a, st, ev); break;
     case 9: if constexpr (MT == 1 && EPI == EPI_SWIGLU) return launch_one<EPI, MT, 9>(nw, a, st, ev); break;
     case 10: if constexpr (MT == 1 && EPI == EPI_SWIGLU) return launch_one<EPI, MT, 10>(nw, a, st, ev); break;
   }
@@ -1711,7 +1701,7 @@ hipError_t launch_qkv_attn(int mt, int S, int head_dim, const GemmArgs& g, const
 }
 
 hipError_t launch_gemm(int epi, int mt, int S, int nw, const GemmArgs& a, hipStream_t st, LaunchEvents ev) {
-  if (nw < 4 || nw > 8 || S < 1 || (size_t)nw * S * mt * 1024 > 64 * 1024) return hipErrorInvalidValue;
+  if (nw < 4 || nw > 8 || S < 1 || (size_t)nw * S * mt * 1024 > kGemmLdsMax) return hipErrorInvalidValue;
   // the tiles cover the strips; only gate/up workgroups of 8+ strips may be ragged
   if (a.n_tiles < 1 || (size_t)a.n_tiles * S < (size_t)a.n_strips || (size_t)(a.n_tiles - 1) * S >= (size_t)a.n_strips)
     return hipErrorInvalidValue;

@@ -29,5 +29,20 @@ __device__ __forceinline__ bool better(float v, int i, float bv, int bi) {
   return v > bv || (v == bv && i < bi);
 }
 
+// The best (value, index) over the 16 lanes of a DPP row, in every lane: the
+// same moves as sum16.
+template <int CTRL>
+__device__ __forceinline__ void best_dpp(float& bv, int& bi) {
+  const float ov = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(bv), CTRL, 0xF, 0xF, false));
+  const int oi = __builtin_amdgcn_mov_dpp(bi, CTRL, 0xF, 0xF, false);
+  if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
+}
+__device__ __forceinline__ void best16(float& bv, int& bi) {
+  best_dpp<0xB1>(bv, bi);
+  best_dpp<0x4E>(bv, bi);
+  best_dpp<0x141>(bv, bi);
+  best_dpp<0x140>(bv, bi);
+}
+
 }  // namespace
 }  // namespace pard

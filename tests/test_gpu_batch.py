@@ -177,3 +177,25 @@ def test_llama_8b_1b_full_width_slice_32_slots_batched(B):
         say(f"    max |logit err| {bl.worst:.3g}")
     finally:
         eng.close()
+
+
+@pytest.mark.parametrize("pair,n_slots", [("llama8b_1b", 2), ("llama8b_1b", 4), ("llama8b_1b", 7), ("qwen7b_05b", 3)])
+def test_full_width_small_batches_lockstep(B, pair, n_slots):
+    """18 to 63 rows (two to four row tiles) at full widths: the wide gate/up,
+    split down and lm_head tiles of passes of 17 to 64 rows."""
+    wl = pi.WORKLOADS[pair]
+    vocab, k = 36864, 8
+    t_spec = replace(pi.with_dtype(wl.target, "bf16"), n_layers=1, vocab=vocab)
+    d_spec = replace(pi.with_dtype(wl.draft, "bf16"), n_layers=1, vocab=vocab)
+    prompts = _ragged_prompts(41, n_slots, 8, 40, vocab)
+    say(f"[gpu] {pair} widths, {n_slots} slots: oracle build")
+    target, draft = oracle.build_model(t_spec), oracle.build_model(d_spec)
+    eng = B.Engine(t_spec, d_spec, vocab - 1, max_ctx=96, max_k=k, max_batch=n_slots)
+    try:
+        bl = BatchLockstep(eng, target, draft, prompts, k, vocab - 1, tag=f"{pair} x{n_slots}")
+        bl.prefill()
+        for step in range(2):
+            bl.step(n_tokens=40)
+        say(f"    max |logit err| {bl.worst:.3g}")
+    finally:
+        eng.close()
