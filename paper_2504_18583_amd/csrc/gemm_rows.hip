@@ -22,7 +22,7 @@
 //
 // Against the earlier form (A through registers into a two-deep LDS buffer,
 // one 144 x 256 tile per CU; TFLOP/s): gate/up of the 8B shape, 288 rows 753 ->
-// 810, 512 rows 830 -> 860; 4096 rows, which that form could not hold, 1030-1060
+// 870, 512 rows 830 -> 870; 4096 rows, which that form could not hold, 1030-1060
 // (torch's fp16 matmul at 8192^3: 1260).
 //
 // Blocks are numbered so that the row blocks of one column tile run on the
@@ -30,8 +30,13 @@
 // the later blocks' weight reads then hit that XCD's L2 rather than HBM.
 // Narrow GEMMs split the input dimension (ksplit > 1) to fill the chip; each
 // split writes fp32 partial tiles and k_gemm_rows_red adds them in split
-// order and runs the epilogue, so results are deterministic.  Epilogues: as
-// in the skinny GEMM.
+// order and runs the epilogue, so results are deterministic.
+//
+// Epilogues: as in the skinny GEMM.  Stores of 2 bytes straight from the
+// accumulator layout cost as much as a narrow GEMM, so QKV and the residual go
+// through a transpose within quads of lanes (8 and 16 bytes a lane) and gate/up
+// through LDS: QKV 8B at 4096 rows 272 -> 204 us, at 517 rows 54 -> 42; O 165 ->
+// 144; 1B QKV 111 -> 69.
 #include "attn_tile.h"
 #include "gemm_util.h"
 #include "pard_internal.h"
@@ -46,18 +51,18 @@ namespace pard {
 namespace {
 
 // Tile variants: MB row tiles, CG wavefronts of NS strips, and the time of one
-// k-block in us with one and with two workgroups on a CU (measured, 8B
-// shapes), which the plan's cost model uses.
+// k-block in us with one and with two workgroups on a CU, which the plan's cost
+// model uses (plan_rows).
 struct Variant {
   int mb, cg, ns;
   float us1, us2;      // us2 = 0: one workgroup per CU
 };
 constexpr Variant kVariants[] = {
-    {8, 4, 4, 0.530f, 0.985f},   // 128 x 256, two workgroups per CU: prefill chunks
-    {9, 8, 2, 0.640f, 0.f},      // 144 x 256 in eight wavefronts
-    {8, 8, 2, 0.510f, 0.f},      // 128 x 256 in eight wavefronts
-    {9, 4, 2, 0.380f, 0.850f},   // 144 x 128: narrow weights
-    {8, 4, 2, 0.300f, 0.770f},   // 128 x 128
+    {8, 8, 2, 0.42f, 0.f},       // 128 x 256 in eight wavefronts: prefill chunks
+    {9, 8, 2, 0.53f, 0.f},       // 144 x 256 in eight wavefronts: 32 conversations' nine rows
+    {9, 4, 2, 0.30f, 0.58f},     // 144 x 128: narrow weights
+    {8, 4, 2, 0.26f, 0.56f},     // 128 x 128
+    {6, 4, 2, 0.26f, 0.44f},     // 96 x 128: few rows
 };
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
@@ -71,6 +76,28 @@ __device__ __forceinline__ void static_for(F&& f) {
     f(std::integral_constant<int, B>{});
     static_for<B + 1, E>(f);
   }
+}
+
+// 4 x 4 transpose within each quad of lanes: lane q holds rows 0..3 of column
+// q and gets columns 0..3 of row q (two exchanges, with lane q ^ 1 and q ^ 2).
+// The epilogues use it to read and write 8 and 16 bytes a lane: one memory
+// instruction where the accumulator layout takes four.
+__device__ __forceinline__ f32x4 quad_transpose(f32x4 a, int lane) {
+  const auto xor1 = [](float v) { return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, false)); };
+  const auto xor2 = [](float v) { return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xF, 0xF, false)); };
+  const bool odd = lane & 1, hi = lane & 2;
+  const float r = xor1(odd ? a[0] : a[1]), r2 = xor1(odd ? a[2] : a[3]);
+  // row (q & 1) and row 2 + (q & 1), columns (q & 2) and the next
+  const float p0 = odd ? r : a[0], p1 = odd ? a[1] : r;
+  const float q0 = odd ? r2 : a[2], q1 = odd ? a[3] : r2;
+  const float s0 = xor2(hi ? p0 : q0), s1 = xor2(hi ? p1 : q1);
+  return f32x4{hi ? s0 : p0, hi ? s1 : p1, hi ? q0 : s0, hi ? q1 : s1};
+}
+
+// Four values as fp16, flagged as f16_flagged does.
+__device__ __forceinline__ uint2 pack4_flagged(float a, float b, float c, float d, bool& bad) {
+  const uint32_t h0 = f16_flagged(a, bad), h1 = f16_flagged(b, bad), h2 = f16_flagged(c, bad), h3 = f16_flagged(d, bad);
+  return uint2{h0 | (h1 << 16), h2 | (h3 << 16)};
 }
 
 // 1/rms of R*T/16 rows (T threads) from the producer's per-tile sums of
@@ -129,78 +156,87 @@ __device__ __forceinline__ void rows_epilogue(const GemmArgs& p, const FwdDesc* 
     // a linear pass is one sequence's consecutive positions
     const bool linear = dp->linear != 0;
     const int lin_pos = dp->seq[0].pos0, lin_slot = dp->seq[0].slot;
+    const int tr = g4 * 4 + (c16 & 3), tc = (c16 >> 2) * 4;   // this lane's row and first column once transposed
     static_for<0, MBW>([&](auto mtc) __attribute__((always_inline)) {
       constexpr int mt = decltype(mtc)::value;
       if (row0 + mt * 16 >= row_count) return;       // uniform
-      int pos[4], slot[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int r = min(row0 + mt * 16 + g4 * 4 + i, row_count - 1);
-        pos[i] = linear ? lin_pos + r : dp->pos[r];
-        slot[i] = linear ? lin_slot : dp->slot[r];
-      }
+      const int r = row0 + mt * 16 + tr, rc = min(r, row_count - 1);
+      const int pos = linear ? lin_pos + rc : dp->pos[rc];
+      const size_t cache = (size_t)(linear ? lin_slot : dp->slot[rc]) * p.kv_seq_stride;
+      const float sc = rs_s[mt * 16 + tr];
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
-        const int n = (strip0 + s) * 16 + c16;
-        const bool col_ok = strip0 + s < p.n_strips;
-        const float bias = (col_ok && p.bias) ? p.bias[n] : 0.f;
+        const int n0 = (strip0 + s) * 16;            // (Q, K and V begin at multiples of head_dim)
+        if (strip0 + s >= p.n_strips) continue;      // uniform
+        if (n0 < p.q_dim + p.kv_dim) {               // uniform: Q or K, four columns of one row
+          const int n = n0 + tc;
+          f32x4 y = quad_transpose(acc[mt][s], lane) * sc;
+          if (p.bias) y += *reinterpret_cast<const f32x4*>(p.bias + n);
+          const f32x4 cs = *reinterpret_cast<const f32x4*>(p.rope + (size_t)pos * (p.hd / 2) + ((n % p.hd) >> 1));
+          const float a0 = y[0] * cs[0] - y[1] * cs[1], a1 = y[1] * cs[0] + y[0] * cs[1];
+          const float a2 = y[2] * cs[2] - y[3] * cs[3], a3 = y[3] * cs[2] + y[2] * cs[3];
+          bool bad_r = false;
+          const uint2 v = pack4_flagged(a0, a1, a2, a3, bad_r);
+          if (r < row_count) {
+            bad |= bad_r;
+            const int c = n - p.q_dim;
+            uint16_t* dst = n0 < p.q_dim ? p.out + (size_t)r * p.ld_out + n
+                                         : p.kc + cache + (size_t)(c / p.hd) * p.cap * p.hd + k_index(pos, c % p.hd, p.hd);
+            *reinterpret_cast<uint2*>(dst) = v;
+          }
+        } else {                                     // V: one column of four rows
+          const int n = n0 + c16, c = n - p.q_dim - p.kv_dim;
+          const float bias = p.bias ? p.bias[n] : 0.f;
+          const int rl = mt * 16 + g4 * 4, r0 = row0 + rl;
+          const size_t head = (size_t)(c / p.hd) * (p.cap / 32);
+          float y[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int rl = mt * 16 + g4 * 4 + i, r = row0 + rl;
-          float y = acc[mt][s][i] * rs_s[rl] + bias;
-          // rotary partner column (n ^ 1) is in lane l ^ 1 (DPP quad swap)
-          const float partner = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, y), 0xB1,
-                                                                                   0xF, 0xF, false));
-          if (col_ok && r < row_count) {
-            const size_t cache = (size_t)slot[i] * p.kv_seq_stride;
-            if (n < p.q_dim + p.kv_dim) {
-              const float2 cs = p.rope[(size_t)pos[i] * (p.hd / 2) + ((n % p.hd) >> 1)];
-              y = (n & 1) ? (y * cs.x + partner * cs.y) : (y * cs.x - partner * cs.y);
-            }
-            const uint16_t b = f16_flagged(y, bad);
-            if (n < p.q_dim) {
-              p.out[(size_t)r * p.ld_out + n] = b;
-            } else if (n < p.q_dim + p.kv_dim) {
-              const int c = n - p.q_dim;
-              p.kc[cache + (size_t)(c / p.hd) * p.cap * p.hd + k_index(pos[i], c % p.hd, p.hd)] = b;
-            } else {
-              const int c = n - p.q_dim - p.kv_dim;
-              const size_t blk = (size_t)(c / p.hd) * (p.cap / 32) + (pos[i] >> 5);
-              p.vc[cache + (blk * p.hd + (c % p.hd)) * 32 + v_slot(pos[i] & 31)] = b;
-            }
+          for (int i = 0; i < 4; ++i) y[i] = acc[mt][s][i] * rs_s[rl + i] + bias;
+          if (linear && !(lin_pos & 3) && r0 + 3 < row_count) {
+            // four consecutive keys from a multiple of four on are contiguous
+            const int ps = lin_pos + r0;
+            *reinterpret_cast<uint2*>(p.vc + (size_t)lin_slot * p.kv_seq_stride +
+                                      ((head + (ps >> 5)) * p.hd + (c % p.hd)) * 32 + v_slot(ps & 31)) =
+                pack4_flagged(y[0], y[1], y[2], y[3], bad);
+          } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              if (r0 + i < row_count) {
+                const int ps = linear ? lin_pos + r0 + i : dp->pos[r0 + i];
+                const size_t at = (size_t)(linear ? lin_slot : dp->slot[r0 + i]) * p.kv_seq_stride;
+                p.vc[at + ((head + (ps >> 5)) * p.hd + (c % p.hd)) * 32 + v_slot(ps & 31)] = f16_flagged(y[i], bad);
+              }
           }
         }
       }
     });
     flag_range(bad, p.ovf);
   } else if constexpr (EPI == EPI_RESID) {
+    const int tr = g4 * 4 + (c16 & 3), tc = (c16 >> 2) * 4;   // this lane's row and first column once transposed
     static_for<0, MBW>([&](auto mtc) __attribute__((always_inline)) {
       constexpr int mt = decltype(mtc)::value;
       if (row0 + mt * 16 >= row_count) return;       // uniform
-      float sq[4] = {0.f, 0.f, 0.f, 0.f};
+      const int r = row0 + mt * 16 + tr;
+      float sq = 0.f;
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
-        const int n = (strip0 + s) * 16 + c16;
+        const int n = (strip0 + s) * 16 + tc;
         if (strip0 + s >= p.n_strips) continue;      // uniform
-        const float g = p.g_next[n];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int r = row0 + mt * 16 + g4 * 4 + i;
-          if (r < row_count) {
-            const size_t o = (size_t)r * p.ldx + n;
-            const float xn = p.x[o] + acc[mt][s][i];   // residual + projection
-            p.x[o] = xn;
-            p.xg[act_index(r, n, p.act_rows)] = f16_flagged(xn * g, bad);
-            sq[i] += xn * xn;
-          }
+        const f32x4 y = quad_transpose(acc[mt][s], lane);
+        if (r < row_count) {
+          f32x4* xp = reinterpret_cast<f32x4*>(p.x + (size_t)r * p.ldx + n);
+          const f32x4 g = *reinterpret_cast<const f32x4*>(p.g_next + n);
+          const f32x4 xn = *xp + y;                  // residual + projection
+          *xp = xn;
+          *reinterpret_cast<uint2*>(p.xg + act_index(r, n, p.act_rows)) =
+              pack4_flagged(xn[0] * g[0], xn[1] * g[1], xn[2] * g[2], xn[3] * g[3], bad);
+          sq += xn[0] * xn[0] + xn[1] * xn[1] + xn[2] * xn[2] + xn[3] * xn[3];
         }
       }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float t = sum16(sq[i]);
-        const int r = row0 + mt * 16 + g4 * 4 + i;
-        if (c16 == 0 && r < row_count && strip0 < p.n_strips) p.ss_out[(size_t)r * p.ss_stride + ent] = t;
-      }
+      // the row's four lanes (c16, c16 ^ 4, ..): DPP row rotates by 4 and 8
+      sq += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(sq), 0x124, 0xF, 0xF, false));
+      sq += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(sq), 0x128, 0xF, 0xF, false));
+      if (c16 < 4 && r < row_count && strip0 < p.n_strips) p.ss_out[(size_t)r * p.ss_stride + ent] = sq;
     });
     flag_range(bad, p.ovf);
   } else if constexpr (EPI == EPI_SWIGLU) {
@@ -560,11 +596,17 @@ hipError_t launch_epi(int variant, const GemmArgs& a, hipStream_t st, LaunchEven
 }  // namespace
 
 // The variant and input split with the least modelled time at the typical row
-// count: a launch's fixed cost, its rounds of workgroups over the 256 CUs (at
-// the variant's measured time per k-block with one or two on a CU), and for a
-// split the reduction's launch and its fp32 partial tiles, written and read.
+// count: a launch's fixed cost and that of each round of workgroups over the
+// 256 CUs (fill and epilogue), the k-blocks of these rounds at the variant's time
+// with one or two workgroups on a CU, no less than the weights' reading, and for
+// a split its fp32 partial tiles, written and read.  The constants are fitted to
+// 195 measured (shape, rows) points of the 8B, 1B, Qwen2.5-7B and 0.5B layers at
+// 72 to 4096 rows, all variants and splits each: the chosen plan is 1.7 % slower
+// than the fastest one measured on average (15 % at most); constants estimated
+// from a few shapes of the earlier epilogues: 6.4 %.
 // The grid covers max_rows.
 RowsPlan plan_rows(int n_strips, int kb_total, int max_rows, int typ_rows) {
+  constexpr float kLaunchUs = 5.8f, kRoundUs = 1.2f, kWeightBytesPerUs = 5.3e6f, kPartBytesPerUs = 2.1e6f;
   RowsPlan best;
   float best_us = 0.f;
   const int typ = std::max(1, std::min(typ_rows, max_rows));
@@ -572,12 +614,14 @@ RowsPlan plan_rows(int n_strips, int kb_total, int max_rows, int typ_rows) {
     const Variant& k = kVariants[v];
     const int n_tiles = (n_strips + k.cg * k.ns - 1) / (k.cg * k.ns);
     const int blocks = (typ + k.mb * 16 - 1) / (k.mb * 16), max_blocks = (max_rows + k.mb * 16 - 1) / (k.mb * 16);
-    for (int ksplit = 1; ksplit <= std::min(16, std::max(1, kb_total / 8)); ++ksplit) {
+    for (int ksplit = 1; ksplit <= std::min(12, std::max(1, kb_total / 8)); ++ksplit) {
       if (ksplit > 1 && (size_t)ksplit * max_blocks * k.mb * n_strips * 256 > kRowsPartTotal) break;
       const int per_cu = (n_tiles * blocks * ksplit + 255) / 256;
       const float rounds = k.us2 > 0.f ? (per_cu / 2) * k.us2 + (per_cu % 2) * k.us1 : per_cu * k.us1;
-      float us = 6.f + rounds * ((kb_total + ksplit - 1) / ksplit);
-      if (ksplit > 1) us += 6.f + ksplit * (float)((typ + 15) / 16) * n_strips * 1024.f / 3.2e6f;
+      float us = std::max(per_cu * kRoundUs + rounds * ((kb_total + ksplit - 1) / ksplit),
+                          n_strips * (float)kb_total * 1024.f / kWeightBytesPerUs);
+      us += kLaunchUs;
+      if (ksplit > 1) us += ksplit * (float)((typ + 15) / 16) * n_strips * 1024.f / kPartBytesPerUs;
       if (best.variant < 0 || us < best_us) {
         best_us = us;
         best.variant = v;
