@@ -890,6 +890,8 @@ pard_status forward(pard_ctx* c, int w, const PassSpec& ps) {
     ta.logits = M.logits;
     ta.q_logits = c->m[PARD_DRAFT].logits;
     ta.tile_w = (lm_rows ? r_lm.ent_strips : S_lm) * 16;
+    ta.resid_part = c->rows_part;
+    ta.counters = c->split_counters;
     ta.clock = c->clock_dev;
     Timed t(c, cls0 + 7);
     HIP_TRY(c, launch_tail(ta, ps.n_seq, c->stream));

@@ -54,13 +54,28 @@ namespace pard {
 namespace {
 
 // Wavefront reductions and scan in a fixed order (results do not depend on timing).
-__device__ __forceinline__ float wave_sum(float v) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  return v;
-}
+// They stay in the VALU (DPP moves, then the lane swaps): through LDS shuffles
+// they were most of a sampled step's tail.
+__device__ __forceinline__ float wave_sum(float v) { return attn::sum4g(sum16(v)); }
 __device__ __forceinline__ float wave_max(float v) {
-  for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
-  return v;
+  v = fmaxf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, false)));
+  v = fmaxf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xF, 0xF, false)));
+  v = fmaxf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x141, 0xF, 0xF, false)));
+  v = fmaxf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x140, 0xF, 0xF, false)));
+  return attn::max4g(v);
+}
+// The best (value, index) of the wavefront, in every lane.
+__device__ __forceinline__ void wave_best(float& bv, int& bi) {
+  best16(bv, bi);
+  auto swap = [&](const auto v, const auto i) {
+    bv = __uint_as_float(v[0]);
+    bi = (int)i[0];
+    if (better(__uint_as_float(v[1]), (int)i[1], bv, bi)) { bv = __uint_as_float(v[1]); bi = (int)i[1]; }
+  };
+  swap(__builtin_amdgcn_permlane16_swap(__float_as_uint(bv), __float_as_uint(bv), false, false),
+       __builtin_amdgcn_permlane16_swap((unsigned)bi, (unsigned)bi, false, false));
+  swap(__builtin_amdgcn_permlane32_swap(__float_as_uint(bv), __float_as_uint(bv), false, false),
+       __builtin_amdgcn_permlane32_swap((unsigned)bi, (unsigned)bi, false, false));
 }
 __device__ __forceinline__ float wave_incl_scan(float v, int lane) {
   for (int off = 1; off < 64; off <<= 1) {
@@ -1112,21 +1127,17 @@ __device__ __forceinline__ void tile_block_weights(const TailArgs& p, int lmr, i
   }
 }
 
-// (M, S) of lm row `lmr` (one wavefront): S adds the blocks' sums in block order.
-__device__ void row_stats(const TailArgs& p, int lmr, int lane, float* M, float* S) {
-  const float* mv = p.amax_val + (size_t)lmr * p.n_tiles;
-  float m = -INFINITY;
-  for (int t = lane; t < p.n_tiles; t += 64) m = fmaxf(m, mv[t]);
-  m = wave_max(m);
+// S of lm row `lmr` with maximum M (one wavefront): the blocks' sums in block
+// order.
+__device__ float row_sum(const TailArgs& p, int lmr, float M, int lane) {
   float acc = 0.f;
   for (int b0 = 0; b0 < p.n_tiles; b0 += 64 * kScanBatch) {
     float w[kScanBatch];
-    tile_block_weights(p, lmr, b0, m, lane, w);
+    tile_block_weights(p, lmr, b0, M, lane, w);
 #pragma unroll
     for (int u = 0; u < kScanBatch; ++u) acc += wave_sum(w[u]);
   }
-  *M = m;
-  *S = acc;
+  return acc;
 }
 
 // Draw from lm row `lmr` with uniform u (one wavefront; every lane returns the
@@ -1186,17 +1197,18 @@ __device__ int wave_sample(const TailArgs& p, int lmr, float M, float S, float u
 
 // Residual draw at a rejected position: weights max(0, p(x) - q(x)) over the
 // vocabulary, p from the target row zp (M_p, S_p), q from the draft row zq
-// (M_q, S_q).  Block g holds entries [256 g, 256 g + 256), 4 per lane; the
-// wavefronts take blocks round-robin and keep each block's sum in LDS; wave 0
-// then scans the block sums in order and the chosen block inside.  Whole
-// workgroup; returns -1 when the residual has no mass (only through rounding).
-__device__ int block_sample_residual(const TailArgs& p, const float* zp, float Mp, float Sp, const float* zq,
-                                     float Mq, float Sq, float u, float* part_s, int* pick_s) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int V = p.vocab, n_blocks = (V + kResidBlock - 1) / kResidBlock;
-  const float k = p.samp_k, ip = 1.0f / Sp, iq = 1.0f / Sq;
-  auto resid4 = [&](int g, float (&r)[4]) {      // V is a multiple of 16: a lane's 4 entries are all in range or not
-    const int x0 = g * kResidBlock + 4 * lane;
+// (M_q, S_q).  Block g holds entries [256 g, 256 g + 256), 4 per lane.  Whole
+// workgroups: resid_sums leaves the sums of its share of the blocks (wavefront
+// w of workgroup `part` of n_part: blocks 16 part + w, + 16 n_part, ..) in LDS
+// or, where several workgroups share the row, in memory; resid_pick scans all
+// block sums in order and the chosen block inside (-1 when the residual has no
+// mass, only through rounding).
+struct Resid {
+  const float *zp, *zq;
+  float Mp, Mq, k, ip, iq;
+  int V;
+  __device__ __forceinline__ void entries(int g, int lane, float (&r)[4]) const {
+    const int x0 = g * kResidBlock + 4 * lane;     // V is a multiple of 16: a lane's 4 entries are all in range or not
     if (x0 < V) {
       const f32x4 a = *reinterpret_cast<const f32x4*>(zp + x0);
       const f32x4 b = *reinterpret_cast<const f32x4*>(zq + x0);
@@ -1206,22 +1218,38 @@ __device__ int block_sample_residual(const TailArgs& p, const float* zp, float M
     } else {
       r[0] = r[1] = r[2] = r[3] = 0.f;
     }
-  };
-  for (int g0 = wave; g0 < n_blocks; g0 += 16 * kScanBatch) {
+  }
+};
+
+__device__ void resid_sums(const Resid& q, int part, int n_part, float* part_s, float* part_g) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, step = 16 * n_part;
+  const int n_blocks = (q.V + kResidBlock - 1) / kResidBlock;
+  for (int g0 = 16 * part + wave; g0 < n_blocks; g0 += step * kScanBatch) {
     float r[kScanBatch][4];
 #pragma unroll
     for (int v = 0; v < kScanBatch; ++v) {
-      const int g = g0 + 16 * v;
-      if (g < n_blocks) resid4(g, r[v]);
+      const int g = g0 + step * v;
+      if (g < n_blocks) q.entries(g, lane, r[v]);
       else r[v][0] = r[v][1] = r[v][2] = r[v][3] = 0.f;
     }
 #pragma unroll
     for (int v = 0; v < kScanBatch; ++v) {
+      const int g = g0 + step * v;
+      if (g >= n_blocks) break;                      // uniform
       const float t = wave_sum(((r[v][0] + r[v][1]) + r[v][2]) + r[v][3]);
-      const int g = g0 + 16 * v;
-      if (lane == 0 && g < n_blocks) part_s[g] = t;
+      if (lane == 0) {
+        if (n_part > 1)      // read by another workgroup of this launch: device scope
+          __hip_atomic_store(part_g + g, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else
+          part_s[g] = t;
+      }
     }
   }
+}
+
+__device__ int resid_pick(const Resid& q, float u, const float* part_s, int* pick_s) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int n_blocks = (q.V + kResidBlock - 1) / kResidBlock;
   __syncthreads();
   if (wave == 0) {
     float total = 0.f;
@@ -1251,7 +1279,7 @@ __device__ int block_sample_residual(const TailArgs& p, const float* zp, float M
       if (gsel < 0) gsel = 0;   // not reached: total > 0 means some block has mass
       // inside the block: lane sums in lane order, then the lane's 4 entries
       float r[4];
-      resid4(gsel, r);
+      q.entries(gsel, lane, r);
       const float ls = ((r[0] + r[1]) + r[2]) + r[3];
       const float incl = wave_incl_scan(ls, lane);
       const uint64_t hit = __ballot(ls > 0.f && incl > rem);
@@ -1284,7 +1312,8 @@ __device__ int block_sample_residual(const TailArgs& p, const float* zp, float M
 __device__ void clock_tail_start(const TailArgs& p) {
   if (p.tail != TAIL_VERIFY) return;
   const unsigned long long t = wall_clock64();
-  p.clock->tail_start = t;
+  // (device scope: the tail may end in another workgroup)
+  __hip_atomic_store(&p.clock->tail_start, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   p.clock->verify_ticks += t - p.clock->pass_start[0];
 }
 __device__ void clock_tail_end(const TailArgs& p) {
@@ -1293,7 +1322,7 @@ __device__ void clock_tail_end(const TailArgs& p) {
   if (p.tail == TAIL_DRAFT || p.tail == TAIL_VSD_DRAFT) {
     c->draft_ticks += t - c->pass_start[1];
   } else if (p.tail == TAIL_VERIFY) {
-    c->accept_ticks += t - c->tail_start;
+    c->accept_ticks += t - __hip_atomic_load(&c->tail_start, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     c->step_end[c->n_steps % kStepRing] = t;
     ++c->n_steps;
   }
@@ -1301,14 +1330,16 @@ __device__ void clock_tail_end(const TailArgs& p) {
 
 __global__ __launch_bounds__(1024) void k_lm_tail(const TailArgs p) {
   __shared__ int res_s[kMaxK + 1];
+  __shared__ float Ms[kMaxK + 1], Ss[kMaxK + 1];   // sampling: the rows' maxima and normalisers
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const FwdDesc* dp = p.desc;
   const int sj = blockIdx.x;
   if (sj >= dp->n_seq) return;                    // uniform: the whole block leaves
   // block 0 keeps the clock; with several sequences k_stage (the kernel after
   // this one) ends the phase
+  const int part = blockIdx.y, n_part = gridDim.y;   // workgroups of a sequence (sampled verify passes)
   const bool clock = p.clock && blockIdx.x == 0;
-  if (clock && tid == 0) clock_tail_start(p);
+  if (clock && part == 0 && tid == 0) clock_tail_start(p);
   const PassSeq ps = dp->seq[sj];
   const int rows = min(ps.lm_rows, kMaxK + 1);
   for (int r = wave; r < rows; r += 16) {
@@ -1329,12 +1360,11 @@ __global__ __launch_bounds__(1024) void k_lm_tail(const TailArgs p) {
       for (int u = 0; u < 16; ++u)
         if (better(xv[u], xi[u], bv, bi)) { bv = xv[u]; bi = xi[u]; }
     }
-    for (int off = 32; off > 0; off >>= 1) {
-      const float ov = __shfl_xor(bv, off);
-      const int oi = __shfl_xor(bi, off);
-      if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
+    wave_best(bv, bi);
+    if (lane == 0) {
+      res_s[r] = (bi >= 0 && bi < p.vocab) ? bi : 0;
+      Ms[r] = bv;
     }
-    if (lane == 0) res_s[r] = (bi >= 0 && bi < p.vocab) ? bi : 0;
   }
   const bool sampling =
       p.samp_k > 0.f && (p.tail == TAIL_PREFILL || p.tail == TAIL_DRAFT || p.tail == TAIL_VERIFY);
@@ -1350,15 +1380,13 @@ __global__ __launch_bounds__(1024) void k_lm_tail(const TailArgs p) {
     // from their rows; a verify pass runs the keep tests in order and draws
     // the step's last token from the residual (first rejection) or from the
     // bonus row (all kept)
-    __shared__ float Ms[kMaxK + 1], Ss[kMaxK + 1];
     __shared__ float part_s[kMaxResidBlocks];
-    __shared__ int pick_s[2], a_s, tok_s;
+    __shared__ int pick_s[2], a_s, tok_s, last_s;
     SeqState* st = p.states + ps.slot;
     const int draw = st->draw;
-    for (int r = wave; r < rows; r += 16) {
-      float M, S;
-      row_stats(p, ps.lm0 + r, lane, &M, &S);
-      if (lane == 0) { Ms[r] = M; Ss[r] = S; }
+    for (int r = wave; r < rows; r += 16) {          // (the wavefront that found the row's maximum)
+      const float S = row_sum(p, ps.lm0 + r, Ms[r], lane);
+      if (lane == 0) Ss[r] = S;
     }
     __syncthreads();
     if (p.tail == TAIL_DRAFT || p.tail == TAIL_PREFILL) {
@@ -1397,13 +1425,31 @@ __global__ __launch_bounds__(1024) void k_lm_tail(const TailArgs p) {
       __syncthreads();
       const int a = a_s;
       const float u = sample_uniform(p.seed, ps.slot, draw, a, PURPOSE_LAST);
-      int tok = -1;
+      Resid q{};
       if (a < k) {
         const int2 dm = p.lm_map_draft[ps.slot];
-        tok = block_sample_residual(p, p.logits + (size_t)(ps.lm0 + a) * p.vocab, Ms[a], Ss[a],
-                                    p.q_logits + (size_t)(dm.x + a) * p.vocab, st->qM[a], st->qS[a], u, part_s,
-                                    pick_s);
+        q = Resid{p.logits + (size_t)(ps.lm0 + a) * p.vocab, p.q_logits + (size_t)(dm.x + a) * p.vocab, Ms[a], st->qM[a],
+                  p.samp_k, 1.0f / Ss[a], 1.0f / st->qS[a], p.vocab};
+        resid_sums(q, part, n_part, part_s, p.resid_part + (size_t)sj * kMaxResidBlocks);
       }
+      // The row's workgroups count themselves in, with their sums and their reads
+      // of the state complete; the last one goes on alone.
+      if (n_part > 1) {
+        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+        __syncthreads();
+        if (tid == 0) {
+          const int prev = __hip_atomic_fetch_add(p.counters + sj, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          last_s = prev == n_part - 1;
+          if (prev == n_part - 1) __hip_atomic_store(p.counters + sj, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+        if (!last_s) return;                          // uniform over the workgroup
+        if (a < k)
+          for (int g = tid; g < (p.vocab + kResidBlock - 1) / kResidBlock; g += 1024)
+            part_s[g] = __hip_atomic_load(p.resid_part + (size_t)sj * kMaxResidBlocks + g, __ATOMIC_RELAXED,
+                                          __HIP_MEMORY_SCOPE_AGENT);
+      }
+      const int tok = a < k ? resid_pick(q, u, part_s, pick_s) : -1;
       if (tok < 0) {                                // bonus row (or a residual without mass)
         if (wave == 0) {
           const int x = wave_sample(p, ps.lm0 + a, Ms[a], Ss[a], u, lane);
@@ -1724,7 +1770,17 @@ hipError_t launch_gemm(int epi, int mt, int S, int nw, const GemmArgs& a, hipStr
 
 hipError_t launch_tail(const TailArgs& a, int n_seq, hipStream_t st) {
   if (n_seq < 1 || n_seq > kMaxPassSeqs) return hipErrorInvalidValue;
-  k_lm_tail<<<n_seq, 1024, 0, st>>>(a);
+  // A sampled verify pass draws from a whole row of the vocabulary: one
+  // workgroup per 16 blocks of it (one per wavefront), up to 32 per sequence and
+  // 512 in all (152064 entries, one sequence, K = 12: a step's draft and verify
+  // tails 88 us with one workgroup and reductions through shuffles, 48 now; a
+  // vocabulary of 4096 is 16 blocks)
+  int n_part = 1;
+  if (a.samp_k > 0.f && a.tail == TAIL_VERIFY) {
+    if (!a.resid_part || !a.counters) return hipErrorInvalidValue;
+    n_part = std::max(1, std::min({(a.vocab + 16 * kResidBlock - 1) / (16 * kResidBlock), 32, 512 / n_seq}));
+  }
+  k_lm_tail<<<dim3(n_seq, n_part), 1024, 0, st>>>(a);
   return hipGetLastError();
 }
 

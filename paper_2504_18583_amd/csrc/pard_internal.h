@@ -238,6 +238,8 @@ struct TailArgs {
   const float* logits;
   const float* q_logits;
   int tile_w;
+  float* resid_part;      // sampled verify pass: block sums of the residual draw, kMaxSampleVocab / 256 per sequence
+  int* counters;          // and its workgroups' arrivals, one per sequence (zero between launches)
   PhaseClock* clock;      // pass-boundary clock (phase times of the fused loop)
 };
 

@@ -341,3 +341,35 @@ def test_batched_sampling_decisions_per_slot(B):
                         assert (a, emitted[a]) == (ra, rtok), f"slot {s} step {step}"
     finally:
         eng.close()
+
+
+@pytest.mark.parametrize("vocab,slots", [(4112, [0]), (20000, [2, 0, 1]), (36864, [0, 1])])
+def test_sampling_decisions_wide_vocabulary(B, vocab, slots):
+    """The residual draw shared by several workgroups (one per 4096 vocabulary
+    entries): every slot's keep count and last token equal the rule applied in
+    fp64 to its own GPU logits, away from decision boundaries."""
+    wl, t_spec, d_spec = _tiny()
+    t_spec, d_spec = replace(t_spec, vocab=vocab), replace(d_spec, vocab=vocab)
+    temp, seed, k = 0.2, 7, 4
+    eng = B.Engine(t_spec, d_spec, vocab - 1, max_ctx=128, max_k=k, max_batch=len(slots))
+    rejected = 0
+    try:
+        eng.set_sampling(temp, seed)
+        for s in slots:
+            eng.prefill([int(x) for x in pi.gen_prompt(60 + s, vocab, 18 + 5 * s)], seq=s)
+        for step in range(4):
+            lt = {s: eng.kv_len(B.PARD_TARGET, seq=s) for s in slots}
+            res, _ = eng.generate_batch(slots, k, 64, max_steps=1)
+            for s, toks in zip(slots, res):
+                qg = S.probs(eng.read_logits(B.PARD_DRAFT, k, seq=s), temp)
+                pg = S.probs(eng.read_logits(B.PARD_TARGET, k + 1, seq=s), temp)
+                cands = [S.sample_index(qg[j], S.uniform(seed, s, step, j, S.PURPOSE_DRAFT)) for j in range(k)]
+                a = eng.kv_len(B.PARD_TARGET, seq=s) - lt[s] - 1
+                rejected += a < k
+                if all(m >= SELF_TOL for m in draft_margins(qg, cands, seed, s, step)):
+                    ra, rtok = S.keep_decisions(cands, pg, qg, seed, s, step)
+                    if verify_margin(cands, pg, qg, ra, rtok, seed, s, step) >= SELF_TOL:
+                        assert (a, toks[1:][a]) == (ra, rtok), f"slot {s} step {step}"
+        assert rejected > 0
+    finally:
+        eng.close()
