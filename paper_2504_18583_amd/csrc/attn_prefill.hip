@@ -149,7 +149,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const AttnArgs p) {
 #pragma unroll
       for (int t = 0; t < NQ; ++t) {
         // (the first stage holds key 0, which every row sees: m is finite from there on)
-        const float m_new = fmaxf(m[t], max4g(mx[t]));
+        const float mr = max4g(mx[t]);
+        const float m_new = mr > m[t] + kLazy ? mr : m[t];   // (each row by itself, whatever its neighbours do)
         const float corr = __builtin_amdgcn_exp2f(m[t] - m_new);
         m[t] = m_new;
         l[t] *= corr;

@@ -696,17 +696,15 @@ pard_status forward(pard_ctx* c, int w, const PassSpec& ps) {
   const int n_qblocks = pre_nqt ? ceil_div(qpairs, 64 * pre_nqt) : ceil_div(qpairs, 16 * nqt);
   if (pre_nqt) nqt = pre_nqt;
   int split_len = wide ? ceil_div(l_bound, 128) * 128 : kAttnChunk;
-  // row-block passes over several sequences (batched decode): 1024-key
-  // chunks (batch-32 step 15.5 ms with 256, 15.4 with 512, 15.2 with 1024;
-  // whole contexts, up to 2048 keys, 16.3)
-  if (rows && ps.n_seq > 1) split_len = kAttnBatchChunk;
-  // decode passes over long contexts and single-sequence prefill chunks: the
-  // shortest chunk (a multiple of 128 keys) that keeps the grid within one
-  // workgroup per CU (16k keys, 8B/1B step: 5.33 ms with 256-key chunks, 5.06
-  // with 1024, 4.91 with 640; 16k-token prefill 839 -> 807 ms)
-  if (!wide && (!rows || ps.n_seq == 1)) {
+  // other passes: the shortest chunk (a multiple of 128 keys) that keeps the
+  // grid within one workgroup per CU, and several chunks of about the same
+  // length (16k keys, 8B/1B step: 5.33 ms with 256-key chunks, 5.06 with 1024,
+  // 4.91 with 640; 32 sequences of 256-2048 keys, 9 rows each, 8B: one chunk
+  // 32 us, 1024 keys 36 and the merge)
+  if (!wide) {
     const int per = std::max(1, kAttnDecodeWGs / (ps.n_seq * s.n_kv_heads * n_qblocks));
     split_len = std::min(kAttnLongChunkMax, std::max(split_len, ceil_div(ceil_div(l_bound, per), 128) * 128));
+    split_len = ceil_div(ceil_div(l_bound, ceil_div(l_bound, split_len)), 128) * 128;
   }
   // (one chunk writes no records)
   while (split_len < l_bound && (int64_t)ps.n_seq * n_qblocks * ceil_div(l_bound, split_len) > kAttnRecords) split_len *= 2;

@@ -199,3 +199,30 @@ def test_full_width_small_batches_lockstep(B, pair, n_slots):
         say(f"    max |logit err| {bl.worst:.3g}")
     finally:
         eng.close()
+
+
+@pytest.mark.parametrize("heads,kv,hd,n_slots,lo,hi", [
+    (32, 8, 128, 32, 200, 700),      # whole contexts, three query tiles, four wavefronts
+    (32, 8, 64, 20, 100, 600),       # whole contexts, eight wavefronts
+    (16, 4, 128, 16, 900, 1500),     # key chunks of 384 and their merge; slots that end chunks early
+    (28, 4, 64, 12, 900, 1500),      # two query groups of four and less tiles
+    (8, 4, 128, 24, 300, 900),       # two query tiles
+])
+def test_batched_attention_chunks_lockstep(B, heads, kv, hd, n_slots, lo, hi):
+    """Batched decode attention over key chunks longer than 256 keys: ragged
+    contexts that end inside a tile, a wavefront's share and a chunk."""
+    wl, t_spec, d_spec = _tiny()
+    t_spec = replace(t_spec, n_layers=1, n_heads=heads, n_kv_heads=kv, head_dim=hd)
+    d_spec = replace(d_spec, n_layers=1, n_heads=heads, n_kv_heads=kv, head_dim=hd)
+    prompts = _ragged_prompts(51, n_slots, lo, hi, t_spec.vocab)
+    target, draft = oracle.build_model(t_spec), oracle.build_model(d_spec)
+    eng = B.Engine(t_spec, d_spec, wl.mask_id, max_ctx=hi + 96, max_k=8, max_batch=n_slots)
+    try:
+        bl = BatchLockstep(eng, target, draft, prompts, 8, wl.mask_id, tag=f"{heads}/{kv}x{hd}")
+        bl.prefill()
+        for step in range(2):
+            say(f"[gpu] batched attention {heads}/{kv} heads of {hd}, {n_slots} slots: step {step}")
+            bl.step(n_tokens=40)
+        say(f"    max |logit err| {bl.worst:.3g}")
+    finally:
+        eng.close()

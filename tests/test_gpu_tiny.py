@@ -249,6 +249,26 @@ def test_rewind_reproduces_draft_logits(eng, B):
     assert c1 == c2 and np.array_equal(l1, l2)
 
 
+@pytest.mark.parametrize("at", [32, 77, 78, 79])
+def test_reingest_from_any_position(models, B, at):
+    """A linear pass of more than 64 rows from positions of every remainder
+    modulo 4 (the keys stored together) leaves the caches of a whole prefill."""
+    target, draft = models
+    prompt = [int(x) for x in pi.gen_prompt(13, WL.target.vocab, 301)]
+    eng = B.Engine(T_SPEC, D_SPEC, WL.mask_id, max_ctx=400, max_k=6)
+    try:
+        hist = prompt + [eng.prefill(prompt)]
+        eng.kv_truncate(B.PARD_DRAFT, at)
+        eng.draft(hist, 6)
+        cache = oracle.KVCache(draft)
+        oracle.fill_cache(draft, cache, prompt)
+        _, ref = oracle.draft_step(draft, cache, hist[-1:], 6, WL.mask_id)
+        worst = assert_logits_close(eng.read_logits(B.PARD_DRAFT, 6), ref, f"draft logits after re-ingesting from {at}")
+        say(f"    from {at}: max |logit err| {worst:.3g}")
+    finally:
+        eng.close()
+
+
 def test_runs_are_bitwise_deterministic(eng, B):
     say("[gpu] tiny: determinism")
     outs = []
