@@ -459,10 +459,10 @@ def bench_cod(args) -> int:
         "device_ms_per_step": round(dev_ms, 4),
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": PEAK_HBM_GBPS, "unit": "GB/s",
                      "frac": round(achieved / PEAK_HBM_GBPS, 4), "traffic": None,
-                     "kernel": "k_cod (one 256-thread workgroup per sample)",
+                     "kernel": "k_cod (one workgroup per sample)",
                      "bytes_per_launch": algo_bytes,
                      "note": "HIP events around each k_cod launch on its stream (pard_cod_build's kernel_ms); "
-                             "bound by per-subtask LDS sorts and barriers, not by HBM"},
+                             "bound by the chain of per-subtask selections in LDS, not by HBM"},
     }
     if not args.no_cpu_baseline:
         from oracle import cod
