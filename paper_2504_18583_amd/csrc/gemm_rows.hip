@@ -504,6 +504,8 @@ __global__ __launch_bounds__(64 * CG, 2) void k_gemm_rows(const GemmArgs p) {
         if (strip0 + s < p.n_strips)                 // uniform
           *reinterpret_cast<f32x4*>(part + ((size_t)mt * p.n_strips + strip0 + s) * 256 + lane * 4) = acc[mt][s];
     });
+    // (the clamped loads still in flight land before the workgroup gives its LDS back)
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
     return;
   }
   // the clamped loads still in flight must not land in LDS that the epilogue
