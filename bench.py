@@ -38,16 +38,16 @@ SAMPLING_T, SAMPLING_SEED = 1.0, 2504   # speculative-sampling measurement besid
 # scaled by a copy of known size); valid only while the kernel source is unchanged:
 # the 8B gate/up GEMM launched on its own, and the 8B decode layer's one launch
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_gemm_swiglu_8b_gateup_traffic.txt")
-KERNEL_SOURCES = [os.path.join(ROOT, "paper_2504_18583_amd", "csrc", f) for f in ("gemm.hip", "pard_internal.h")]
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_2504_18583_amd", "csrc", f) for f in ("gemm.hip", "gemm_plan.h", "pard_internal.h")]
 LAYER_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_qkv_attn_8b_layer_traffic.txt")
 LAYER_SOURCES = [os.path.join(ROOT, "paper_2504_18583_amd", "csrc", f)
-                 for f in ("gemm.hip", "attn_tile.h", "pard_internal.h")]
+                 for f in ("gemm.hip", "gemm_plan.h", "attn_tile.h", "pard_internal.h")]
 # measured HBM traffic of whole decode steps of the 8B/1B K = 8 workload (every
 # kernel of the step), valid while the decode path's sources are unchanged
 STEP_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "step_8b_1b_k8_counters.txt")
 STEP_SOURCES = [os.path.join(ROOT, "paper_2504_18583_amd", "csrc", f)
                 for f in ("attention.hip", "attn_tile.h", "device_init.h", "device_init.hip", "engine.hip",
-                          "gemm.hip", "pard_internal.h")]
+                          "gemm.hip", "gemm_plan.h", "pard_internal.h")]
 
 
 def log(msg: str) -> None:

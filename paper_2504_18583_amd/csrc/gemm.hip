@@ -85,10 +85,6 @@ __device__ __forceinline__ float wave_incl_scan(float v, int lane) {
   return v;
 }
 
-// LDS of a workgroup's wavefront partials (launch_gemm): four wavefronts of 7
-// strips and 4 row tiles.
-constexpr size_t kGemmLdsMax = 112 * 1024;
-
 // Input iterations per wavefront that a fused gate/up tile may take from LDS.
 constexpr int kGuPreMax = 8;
 
@@ -1487,7 +1483,6 @@ __global__ __launch_bounds__(256) void k_stage(const TailArgs p) {
 template <int EPI, int MT, int S>
 hipError_t launch_one(int nw, const GemmArgs& a, hipStream_t st, LaunchEvents ev) {
   const size_t lds = (size_t)nw * S * MT * 256 * sizeof(float);
-  if (nw > 8) return hipErrorInvalidValue;
   if (lds > 64 * 1024) {   // (wide tiles of several row tiles: above the default limit)
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm<MT, S, EPI>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -1502,16 +1497,22 @@ hipError_t launch_one(int nw, const GemmArgs& a, hipStream_t st, LaunchEvents ev
   return hipGetLastError();
 }
 
+template <int EPI, int MT, int S>
+hipError_t launch_if(int nw, const GemmArgs& a, hipStream_t st, LaunchEvents ev) {
+  if constexpr (gemm_instance(EPI, MT, S)) return launch_one<EPI, MT, S>(nw, a, st, ev);
+  return hipErrorInvalidValue;
+}
+
 template <int EPI, int MT>
 hipError_t launch_s(int S, int nw, const GemmArgs& a, hipStream_t st, LaunchEvents ev) {
   switch (S) {
-    case 1: return launch_one<EPI, MT, 1>(nw, a, st, ev);
-    case 2: return launch_one<EPI, MT, 2>(nw, a, st, ev);
-    case 4: if constexpr (EPI == EPI_SWIGLU || EPI == EPI_LOGITS) return launch_one<EPI, MT, 4>(nw, a, st, ev); break;
-    case 7: if constexpr (EPI == EPI_SWIGLU) return launch_one<EPI, MT, 7>(nw, a, st, ev); break;
-    case 8: if constexpr ((EPI == EPI_LOGITS && MT <= 3) || (MT == 1 && EPI == EPI_SWIGLU)) return launch_one<EPI, MT, 8>(nw, a, st, ev); break;
-    case 9: if constexpr (MT == 1 && EPI == EPI_SWIGLU) return launch_one<EPI, MT, 9>(nw, a, st, ev); break;
-    case 10: if constexpr (MT == 1 && EPI == EPI_SWIGLU) return launch_one<EPI, MT, 10>(nw, a, st, ev); break;
+    case 1: return launch_if<EPI, MT, 1>(nw, a, st, ev);
+    case 2: return launch_if<EPI, MT, 2>(nw, a, st, ev);
+    case 4: return launch_if<EPI, MT, 4>(nw, a, st, ev);
+    case 7: return launch_if<EPI, MT, 7>(nw, a, st, ev);
+    case 8: return launch_if<EPI, MT, 8>(nw, a, st, ev);
+    case 9: return launch_if<EPI, MT, 9>(nw, a, st, ev);
+    case 10: return launch_if<EPI, MT, 10>(nw, a, st, ev);
   }
   return hipErrorInvalidValue;
 }
@@ -1747,17 +1748,8 @@ hipError_t launch_qkv_attn(int mt, int S, int head_dim, const GemmArgs& g, const
 }
 
 hipError_t launch_gemm(int epi, int mt, int S, int nw, const GemmArgs& a, hipStream_t st, LaunchEvents ev) {
-  if (nw < 4 || nw > 8 || S < 1 || (size_t)nw * S * mt * 1024 > kGemmLdsMax) return hipErrorInvalidValue;
-  // the tiles cover the strips; only gate/up workgroups of 8+ strips may be ragged
-  if (a.n_tiles < 1 || (size_t)a.n_tiles * S < (size_t)a.n_strips || (size_t)(a.n_tiles - 1) * S >= (size_t)a.n_strips)
-    return hipErrorInvalidValue;
-  if (a.n_tiles * S != a.n_strips && !(epi == EPI_SWIGLU && mt == 1 && S >= 8)) return hipErrorInvalidValue;
-  // split input: every range non-empty, partial tiles and counters supplied
-  if (a.ksplit < 1 || a.kb_split < 1 || (a.ksplit - 1) * a.kb_split >= a.kb_total ||
-      a.ksplit * a.kb_split < a.kb_total)
-    return hipErrorInvalidValue;
-  if (a.ksplit > 1 && (!a.part || !a.counters || a.n_tiles > kSplitCounters ||
-                       (size_t)a.n_tiles * a.ksplit * S * mt * 256 > kSplitPartFloats))
+  if (!gemm_launchable(epi, mt, S, nw, a.n_strips, a.kb_total, a.n_tiles, a.ksplit, a.kb_split) ||
+      (a.ksplit > 1 && (!a.part || !a.counters)))
     return hipErrorInvalidValue;
   switch (epi) {
     case EPI_QKV: return launch_mt<EPI_QKV>(mt, S, nw, a, st, ev);

@@ -33,6 +33,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "gemm_plan.h"
+
 namespace pard {
 
 constexpr int kMaxK = 32;
@@ -44,9 +46,6 @@ constexpr int kMaxLmRows = kMaxPassRows;
 constexpr int kMaxPrefillRows = 4096; // rows of one prefill chunk (a linear pass)
 constexpr size_t kRowsPartTotal = (size_t)18 << 20;   // fp32 partial tiles of split row-block GEMMs (72 MiB)
 constexpr int kBlock = 256;
-// skinny GEMM with a split input dimension: tile counters and fp32 partial tiles
-constexpr int kSplitCounters = 4096;
-constexpr size_t kSplitPartFloats = (size_t)4 << 20;
 constexpr int kAttnWaves = 4;      // wavefronts per attention workgroup
 constexpr int kAttnChunk = 256;    // keys per attention workgroup (decode passes): two tiles per wavefront
 constexpr int kAttnWideMaxKeys = 2048;   // decode passes up to this context: one 8-wave workgroup covers all keys
@@ -171,7 +170,6 @@ struct PhaseClock {
   unsigned long long step_end[kStepRing];
 };
 
-enum Epi { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LOGITS = 3 };
 enum Tail { TAIL_NONE = 0, TAIL_PREFILL = 1, TAIL_DRAFT = 2, TAIL_VERIFY = 3, TAIL_VSD_DRAFT = 4 };
 
 struct GemmArgs {

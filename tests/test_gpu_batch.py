@@ -226,3 +226,32 @@ def test_batched_attention_chunks_lockstep(B, heads, kv, hd, n_slots, lo, hi):
         say(f"    max |logit err| {bl.worst:.3g}")
     finally:
         eng.close()
+
+
+@pytest.mark.parametrize("heads,kv,hd", [
+    (32, 32, 128),    # 768 QKV strips: four per workgroup at one row tile
+    (64, 8, 128),     # 640
+    (40, 40, 64),     # 480: two
+    (33, 33, 128),    # 792
+    (43, 43, 64),     # 516, the narrowest that takes four
+    (48, 48, 128),    # 1152: two, beyond one round of four
+])
+@pytest.mark.parametrize("n_slots", [1, 3])
+def test_wide_qkv_weights_lockstep(B, heads, kv, hd, n_slots):
+    """QKV weights wider than 512 strips (many-headed models): one and two row
+    tiles, and a prompt of up to 16 tokens through the skinny GEMM."""
+    wl, t_spec, d_spec = _tiny()
+    t_spec = replace(t_spec, n_layers=1, n_heads=heads, n_kv_heads=kv, head_dim=hd)
+    d_spec = replace(d_spec, n_layers=1, n_heads=heads, n_kv_heads=kv, head_dim=hd)
+    prompts = _ragged_prompts(71, n_slots, 5, 16, t_spec.vocab)
+    target, draft = oracle.build_model(t_spec), oracle.build_model(d_spec)
+    eng = B.Engine(t_spec, d_spec, wl.mask_id, max_ctx=96, max_k=8, max_batch=n_slots)
+    try:
+        bl = BatchLockstep(eng, target, draft, prompts, 8, wl.mask_id, tag=f"{heads}/{kv}x{hd} x{n_slots}")
+        bl.prefill()
+        for step in range(2):
+            say(f"[gpu] wide QKV {heads}/{kv} heads of {hd}, {n_slots} slots: step {step}")
+            bl.step(n_tokens=40)
+        say(f"    max |logit err| {bl.worst:.3g}")
+    finally:
+        eng.close()
