@@ -93,21 +93,17 @@ __global__ __launch_bounds__(64 * NW, 2) void k_attn_chunk(const AttnArgs p) {
   const int n_my = (n_t - wave + NW - 1) / NW;     // (none: the wavefront loads nothing and adds nothing)
 
   const size_t cache = (size_t)d.slot * p.kv_seq_stride + (size_t)kvh * p.cap * HD;
-  const __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p.kc) + cache, 0,
-                                                                        p.cap * HD * 2, kRsrcWord3);
-  const __amdgpu_buffer_rsrc_t vrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p.vc) + cache, 0,
-                                                                        p.cap * HD * 2, kRsrcWord3);
   u32x4* const kw = k_s + wave * FR * 64;
   u32x4* const vw = v_s + wave * FR * 64;
-  auto load = [&](const __amdgpu_buffer_rsrc_t rs, u32x4* dst, int voff, int it) __attribute__((always_inline)) {
-    const int soff = ((k_begin >> 5) + wave + NW * it) * (FR * 1024);
+  auto load = [&](const uint16_t* head, u32x4* dst, int voff, int it) __attribute__((always_inline)) {
+    const __amdgpu_buffer_rsrc_t rs = kv_tile_rsrc<HD>(head, (k_begin >> 5) + wave + NW * it);
 #pragma unroll
     for (int j = 0; j < FR; ++j)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(dst + j * 64), 16, voff,
-                                               soff + j * 1024, 0, 0);
+                                               j * 1024, 0, 0);
   };
-  auto load_k = [&](int it) __attribute__((always_inline)) { load(krs, kw, lane * 16, it); };
-  auto load_v = [&](int it) __attribute__((always_inline)) { load(vrs, vw, c16 * 64 + g4 * 16, it); };
+  auto load_k = [&](int it) __attribute__((always_inline)) { load(p.kc + cache, kw, lane * 16, it); };
+  auto load_v = [&](int it) __attribute__((always_inline)) { load(p.vc + cache, vw, c16 * 64 + g4 * 16, it); };
 
   // Q fragments (B operand): pair t*16 + c16, dims ks*32 + 8*g4 ..; pairs past
   // the group repeat its last one and are not stored

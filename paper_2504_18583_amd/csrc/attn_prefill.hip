@@ -57,17 +57,16 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const AttnArgs p) {
   // this wavefront's K or V half: wavefronts 0, 1 load K, 2, 3 V, the odd ones
   // the stage's second 32 keys
   const size_t cache = (size_t)d.slot * p.kv_seq_stride + (size_t)kvh * p.cap * HD;
-  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t*>(wave < 2 ? p.kc : p.vc) + cache, 0, p.cap * HD * 2, kRsrcWord3);
+  const uint16_t* const half = (wave < 2 ? p.kc : p.vc) + cache;
   const int voff = wave < 2 ? lane * 16 : c16 * 64 + g4 * 16;
   const int last32 = p.cap / 32 - 1;
   // (blocks past the cache re-read its last one: those keys are masked)
   auto load = [&](u32x4* buf, int st) __attribute__((always_inline)) {
-    const int soff = min(st * 2 + (wave & 1), last32) * (FR * 1024);
+    const __amdgpu_buffer_rsrc_t rs = kv_tile_rsrc<HD>(half, min(st * 2 + (wave & 1), last32));
 #pragma unroll
     for (int j = 0; j < FR; ++j)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          rs, (__attribute__((address_space(3))) void*)(buf + (wave * FR + j) * 64), 16, voff, soff + j * 1024, 0, 0);
+          rs, (__attribute__((address_space(3))) void*)(buf + (wave * FR + j) * 64), 16, voff, j * 1024, 0, 0);
   };
   load(b0, 0);
 

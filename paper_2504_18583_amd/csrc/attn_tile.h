@@ -102,6 +102,14 @@ __device__ __forceinline__ void fuse_wait_on(const int* lanes, const int n, int*
 // Wait for every QKV workgroup of the launch.
 __device__ __forceinline__ void fuse_wait(const FuseCtl& f) { fuse_wait_on<kFuseLanes>(f.counters, f.n_prod, f.err); }
 
+// Buffer descriptor of one 32-key tile (HD / 16 KiB) of a KV head's K or V
+// cache.  It starts at the tile: from the cache's start, offsets and the record
+// count would pass 32 bits at the longest contexts (2^24 keys of 128 dims).
+template <int HD>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t kv_tile_rsrc(const uint16_t* head, int tile) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(head) + (size_t)tile * (32 * HD), 0, 64 * HD, kRsrcWord3);
+}
+
 // The attention tile's LDS arrays: Q fragments in B-operand lane order, and the
 // wavefronts' output tiles and softmax statistics for the final merge.  The
 // kernel declares them (static LDS, so the compiler keeps them apart from its
@@ -164,10 +172,12 @@ __device__ __forceinline__ void attn_tile(const AttnArgs& p, const int kvh, cons
   // so it is read with device-scope loads (coherent across XCDs) after the
   // wait; tiles wholly before it were written by earlier launches.
   auto fresh = [&](int it) { return FUSED && tile_key(it) + 31 >= d.pos0; };
-  const __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(kbase), 0,
-                                                                        p.cap * HD * 2, kRsrcWord3);
-  const __amdgpu_buffer_rsrc_t vrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(vbase), 0,
-                                                                        p.cap * HD * 2, kRsrcWord3);
+  // (a fused pass's keys are the first kAttnWideMaxKeys at most: 32-bit offsets)
+  const int kv_bytes = min(p.cap, kAttnWideMaxKeys) * HD * 2;
+  const __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(kbase), 0, kv_bytes,
+                                                                        kRsrcWord3);
+  const __amdgpu_buffer_rsrc_t vrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(vbase), 0, kv_bytes,
+                                                                        kRsrcWord3);
   auto load_k = [&](int tt, int it) {
     const int key0 = tile_key(it);
     if (fresh(it)) {                               // uniform

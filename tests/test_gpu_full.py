@@ -321,3 +321,26 @@ def test_prefill_attention_tiles_lockstep(B, heads, kv, hd, n):
         say(f"    max |logit err| {ls.worst:.3g}")
     finally:
         eng.close()
+
+
+@pytest.mark.parametrize("n", [100, 3000])
+def test_longest_cache_lockstep(B, n):
+    """max_ctx 2^24 at head_dim 128: one KV head's K cache is 4 GiB, past what
+    32-bit record counts and offsets hold.  100 tokens: prefill attention and
+    whole-context decode; 3000: key chunks (32 heads over one KV head, 33
+    rows: 22 query groups, chunks of 384 keys)."""
+    from gpu_common import Lockstep
+    wl = pi.WORKLOADS["tiny"]
+    t_spec = replace(pi.with_dtype(wl.target, "bf16"), n_layers=1, n_heads=32, n_kv_heads=1, head_dim=128)
+    d_spec = replace(pi.with_dtype(wl.draft, "bf16"), n_layers=1)
+    prompt = [int(x) for x in pi.gen_prompt(31, t_spec.vocab, n)]
+    say(f"[gpu] 2^24-key cache, {n} rows")
+    target, draft = oracle.build_model(t_spec), oracle.build_model(d_spec)
+    eng = B.Engine(t_spec, d_spec, wl.mask_id, max_ctx=1 << 24, max_k=32)
+    try:
+        ls = Lockstep(eng, target, draft, prompt, 32, wl.mask_id, tag=f"2^24-key cache {n}")
+        ls.prefill(cache_only_prefix=True)
+        ls.step()
+        say(f"    max |logit err| {ls.worst:.3g}")
+    finally:
+        eng.close()
