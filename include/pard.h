@@ -237,8 +237,10 @@ pard_status pard_generate_ex(pard_ctx *ctx, int32_t n_seq, const int32_t *seqs, 
  *     that last token (K = 0: one token drawn from p_0).
  * Draws use the inverse CDF in token-id order.  The uniforms u come from a
  * SplitMix64 counter generator keyed by (seed, slot, the slot's verify steps
- * since its prefill, position, purpose), so results are reproducible and
- * independent of batching.  T = 0 restores greedy decoding (eq. 2).  Captured
+ * since its prefill, position, purpose), so draws are reproducible and do not
+ * depend on batching; nor do a row's logits, bit for bit, in passes of up to 64
+ * rows over at most 2048 keys (larger passes run other kernels, whose sums round
+ * differently).  T = 0 restores greedy decoding (eq. 2).  Captured
  * step graphs are dropped (rebuilt on the next pard_generate).  With sampling,
  * pard_verify with K > 0 needs this slot's pard_draft of the same K since its
  * last verify (STATE otherwise), and PARD_MODE_VANILLA is UNSUPPORTED.

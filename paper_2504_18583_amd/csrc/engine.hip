@@ -224,13 +224,13 @@ void derive(ModelDev& M, const pard_model_spec& s, int max_ctx) {
   M.nqkv = M.q_dim + 2 * M.kv_dim;
   M.f_pad = ceil_div(s.ffn_dim, 32) * 32;
   M.group = s.n_heads / s.n_kv_heads;
-  M.p_qkv = plan_qkv(M.nqkv, M.d);
+  M.p_qkv = plan_gemm(EPI_QKV, M.nqkv, M.d);
   M.p_o = plan_o(M.d, M.q_dim);
   M.p_gu = plan_gemm(EPI_SWIGLU, 2 * M.f_pad, M.d);
   M.p_d = plan_gemm(EPI_RESID, M.d, M.f_pad);
   M.p_lm = plan_gemm(EPI_LOGITS, s.vocab, M.d);
   // (the row-block GEMM's tiles are at least two strips wide)
-  M.ss_tiles_max = std::max(resid_ss_tiles(M.p_o, 1), ceil_div(M.p_o.n_strips, 2));
+  M.ss_tiles_max = std::max(resid_ss_tiles(M.p_o), ceil_div(M.p_o.n_strips, 2));
 }
 
 // Lays out (base == nullptr: sizes) every device region of a context.
@@ -511,18 +511,13 @@ hipError_t run_gemm(pard_ctx* c, int cls, int epi, int max_rows, const RowsPlan&
     return launch_gemm_rows(epi, r.variant, a, c->stream, ev);
   }
   const int mt = ceil_div(max_rows, 16);
-  int S = pick_S(epi, p.n_strips, mt);
+  const int S = pick_S(epi, p.n_strips, mt);
   a.ksplit = p.ksplit;
-  if (epi == EPI_RESID) {
-    const ResidPlan rp = resid_plan(p, mt);
-    S = rp.S;
-    a.ksplit = rp.ksplit;
-  }
   a.n_tiles = ceil_div(p.n_strips, S);
-  a.kb_split = ceil_div(p.kb_total, a.ksplit);
+  a.kb_split = ceil_div(p.kb_total, p.ksplit);
   a.part = c->rows_part;
   a.counters = c->split_counters;
-  return launch_gemm(epi, mt, S, plan_nw(p, mt), a, c->stream, ev);
+  return launch_gemm(epi, mt, S, p.nw, a, c->stream, ev);
 }
 
 pard_status forward(pard_ctx* c, int w, const PassSpec& ps) {
@@ -535,8 +530,7 @@ pard_status forward(pard_ctx* c, int w, const PassSpec& ps) {
   // row-block plans of the pass's GEMMs; the row sums of squares of the
   // residual GEMMs come in their plan's pieces
   RowsPlan r_qkv, r_o, r_gu, r_d;
-  const int mt_pass = ceil_div(ps.max_rows, 16);
-  int ss_o = resid_ss_tiles(M.p_o, mt_pass), ss_d = resid_ss_tiles(M.p_d, mt_pass);
+  int ss_o = resid_ss_tiles(M.p_o), ss_d = resid_ss_tiles(M.p_d);
   if (rows) {
     auto plan = [&](const GemmPlan& p) { return plan_rows(p.n_strips, p.kb_total, ps.max_rows, typ); };
     r_qkv = plan(M.p_qkv);
@@ -621,13 +615,13 @@ pard_status forward(pard_ctx* c, int w, const PassSpec& ps) {
   const int S_gu = pick_S(EPI_SWIGLU, M.p_gu.n_strips, 1);
   bool fused_gu = false, fused_d = false;
   if (fused_o && c->use_fused_gu && (S_gu == 4 || S_gu == 7) && M.p_gu.ksplit == 1 &&
-      M.p_gu.n_strips % S_gu == 0 && plan_nw(M.p_gu, 1) == 4) {
+      M.p_gu.n_strips % S_gu == 0 && M.p_gu.nw == 4) {
     const int n_qkv = M.p_qkv.n_strips / S_q;
     const int gu_tiles = M.p_gu.n_strips / S_gu;
     // and the down projection (one strip per tile, one input range), whose
     // workgroups wait for every gate/up tile
     const int d_S = c->use_fused_d && M.p_d.ksplit <= 2 && pick_S(EPI_RESID, M.p_d.n_strips, 1) == 1 &&
-                    plan_nw(M.p_d, 1) == 4 ? 1 : 0;
+                    M.p_d.nw == 4 ? 1 : 0;
     const int d_units = d_S ? M.p_d.n_strips * M.p_d.ksplit : 0;
     const int pre_max = std::min(qkv_attn_gu_pre_max(S_q, s.head_dim, M.p_o.kb_total, S_gu, d_S), M.p_gu.kb_total / 4);
     const int pre = c->gu_pre >= 0 ? std::min(c->gu_pre, pre_max) : pre_max;

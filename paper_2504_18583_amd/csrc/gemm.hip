@@ -15,8 +15,8 @@
 // encoding) feed v_mfma_f32_16x16x32_f16 directly.
 //
 // The wavefront partials are summed in LDS in wave order, so results are
-// deterministic; the split depends only on the weight shape and on whether the
-// pass has more than 16 rows.  No workgroup ever waits for another one.
+// deterministic; the split depends only on the weight shape, so a row's sums do
+// not depend on the pass's row count.  No workgroup ever waits for another one.
 //
 // Shapes with few strips also split the input dimension over the grid's y
 // dimension (P contiguous ranges of k-blocks), so that narrow GEMMs still

@@ -52,12 +52,12 @@ inline bool gemm_launchable(int epi, int mt, int S, int nw, int n_strips, int kb
 }
 
 // Tile plan of one skinny GEMM: S strips per workgroup, nw wavefronts splitting
-// the input dimension.  nw depends only on the weight shape and on whether the
-// pass has more than 16 rows, and so does the order of a sum.
+// the input dimension.  nw and ksplit, and with them the order of a sum, depend
+// only on the weight shape: a row's result does not depend on how many other
+// rows its pass has.
 struct GemmPlan {
   int n_strips = 0, kb_total = 0;
   int nw = 4;   // one wavefront per SIMD: more waves per workgroup measured slower at every decode shape
-  int nw_mid = 4;   // the same for passes of 17 rows and more
   int ksplit = 1;   // input ranges of the skinny GEMM
 };
 
@@ -133,48 +133,28 @@ inline GemmPlan plan_gemm(int epi, int n_pad, int k_pad) {
   // A long, narrow residual GEMM (the 1B down projection: 128 strips x 256
   // k-blocks) fills only half the CUs with one workgroup per strip; two input
   // ranges per strip measured 11.8 against 13.6 us.  Shorter or wider shapes
-  // measured slower split (the partial-tile exchange adds ~2 us of tail).
+  // measured slower split (the partial-tile exchange adds ~2 us of tail).  From
+  // 17 rows on two strips over two ranges would serve the 8B and 7B down
+  // projections better (8B: 27.3 -> 26.1 us at 25 rows, 39.4 -> 34.4 at 57; four
+  // conversations' step 2 %), but a row would then be summed in another order
+  // than in a pass of fewer rows.
   if (epi == EPI_RESID && p.n_strips <= 128 && p.kb_total >= 256) p.ksplit = 2;
-  return p;
-}
-
-inline GemmPlan plan_qkv(int n_pad, int k_pad) {
-  GemmPlan p = plan_gemm(EPI_QKV, n_pad, k_pad);
-  // (at 41 rows: 8B 18.2 us with four wavefronts, 17.6 with eight; 1B 9.2, 8.7)
-  p.nw_mid = 8;
   return p;
 }
 
 inline GemmPlan plan_o(int n_pad, int k_pad) {
   GemmPlan p = plan_gemm(EPI_RESID, n_pad, k_pad);
-  // one strip per workgroup: eight wavefronts over the input at one row tile,
-  // as the O units fused into the QKV + attention launch use, so a row's
-  // O-projection is summed in the same order whether or not its decode pass
-  // runs fused (the unfused launch measured 8.3 -> 10.9 us at the 8B shape for
-  // it; 16k-context 8B/1B step 4.53 -> 4.57 ms).  More row tiles have no fused O
-  // and keep four (25 rows, 8B: 10.6 against 13.1 us)
+  // one strip per workgroup: eight partial sums over the input, as the O units
+  // fused into the QKV + attention launch form, so a row's O-projection is
+  // summed in the same order whether or not its pass runs fused (the unfused
+  // launch measured 8.3 -> 10.9 us at the 8B shape for it, 10.6 -> 13.1 at 25 rows;
+  // 16k-context 8B/1B step 4.53 -> 4.57 ms)
   if (pick_S(EPI_RESID, p.n_strips, 1) == 1) p.nw = 8;
   return p;
 }
 
-// Wavefronts per workgroup for a pass of mt row tiles.
-inline int plan_nw(const GemmPlan& p, int mt) { return mt == 1 ? p.nw : p.nw_mid; }
-
-// Strips per workgroup and input ranges of a residual GEMM for a pass of mt row
-// tiles.  A long weight of at most 256 strips takes two strips per workgroup
-// over two input ranges from 17 rows on: half the activation reads in the same
-// number of workgroups, for about 2.5 us of partial-tile exchange (us at 25 and
-// 57 rows: 8B down, 448 k-blocks, 27.3 -> 26.1 and 39.4 -> 34.4; Qwen2.5-7B down,
-// 592 k-blocks, 35.2 -> 32.1 and 50.3 -> 41.8; 8B O, 128 k-blocks, 10.6 -> 13.2).
-struct ResidPlan { int S, ksplit; };
-inline ResidPlan resid_plan(const GemmPlan& p, int mt) {
-  if (mt > 1 && p.ksplit == 1 && p.n_strips > 128 && p.n_strips <= 256 && p.n_strips % 2 == 0 && p.kb_total >= 384)
-    return {2, 2};
-  return {pick_S(EPI_RESID, p.n_strips, mt), p.ksplit};
-}
-
 // Tiles that write row sums of squares per residual GEMM of a pass served by
 // the skinny GEMM (its consumers' ss_tiles).
-inline int resid_ss_tiles(const GemmPlan& p, int mt) { return p.n_strips / resid_plan(p, mt).S; }
+inline int resid_ss_tiles(const GemmPlan& p) { return p.n_strips / pick_S(EPI_RESID, p.n_strips, 1); }
 
 }  // namespace pard

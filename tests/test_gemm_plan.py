@@ -20,17 +20,12 @@ using namespace pard;
 
 // As the engine's run_gemm launches a pass of mt row tiles.
 static int check(const char* name, int epi, const GemmPlan& p, int mt) {
-  int S = pick_S(epi, p.n_strips, mt), ksplit = p.ksplit;
-  if (epi == EPI_RESID) {
-    const ResidPlan r = resid_plan(p, mt);
-    S = r.S;
-    ksplit = r.ksplit;
-  }
-  if (gemm_launchable(epi, mt, S, plan_nw(p, mt), p.n_strips, p.kb_total, ceil_div(p.n_strips, S), ksplit,
-                      ceil_div(p.kb_total, ksplit)) && (epi != EPI_RESID || resid_ss_tiles(p, mt) * S == p.n_strips))
+  const int S = pick_S(epi, p.n_strips, mt);
+  if (gemm_launchable(epi, mt, S, p.nw, p.n_strips, p.kb_total, ceil_div(p.n_strips, S), p.ksplit,
+                      ceil_div(p.kb_total, p.ksplit)) && (epi != EPI_RESID || resid_ss_tiles(p) * S == p.n_strips))
     return 0;
   printf("%s: %d strips x %d k-blocks, %d row tiles -> %d strips, %d wavefronts, %d ranges\n", name, p.n_strips,
-         p.kb_total, mt, S, plan_nw(p, mt), ksplit);
+         p.kb_total, mt, S, p.nw, p.ksplit);
   return 1;
 }
 
@@ -40,7 +35,7 @@ int main() {
   for (int mt = 1; mt <= 4; ++mt)
     for (int kb : kbs) {
       for (int n = 1; n <= 2400; ++n) {
-        bad += check("qkv", EPI_QKV, plan_qkv(n * 16, kb * 32), mt);
+        bad += check("qkv", EPI_QKV, plan_gemm(EPI_QKV, n * 16, kb * 32), mt);
         bad += check("o", EPI_RESID, plan_o(n * 16, kb * 32), mt);
         bad += check("down", EPI_RESID, plan_gemm(EPI_RESID, n * 16, kb * 32), mt);
         if (n % 2 == 0) bad += check("gate/up", EPI_SWIGLU, plan_gemm(EPI_SWIGLU, n * 16, kb * 32), mt);

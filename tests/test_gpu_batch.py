@@ -255,3 +255,41 @@ def test_wide_qkv_weights_lockstep(B, heads, kv, hd, n_slots):
         say(f"    max |logit err| {bl.worst:.3g}")
     finally:
         eng.close()
+
+
+@pytest.mark.parametrize("pair", ["llama8b_1b", "qwen7b_05b"])
+def test_rows_do_not_depend_on_the_pass(B, pair):
+    """Up to 64 rows a row's sums have one order whatever the pass holds beside
+    it: full-width layers give a slot bitwise the same logits stepped alone (one
+    row tile, the one-launch layer) and with 2, 4 or 7 slots (two to four row
+    tiles; draft passes hold up to 2 K rows a slot), and the first rows of a verify
+    pass of 8 candidates are those of one of 24."""
+    wl = pi.WORKLOADS[pair]
+    vocab = 36864
+    t_spec = replace(pi.with_dtype(wl.target, "bf16"), n_layers=2, vocab=vocab)
+    d_spec = replace(pi.with_dtype(wl.draft, "bf16"), n_layers=2, vocab=vocab)
+    prompts = _ragged_prompts(81, 7, 8, 60, vocab)
+
+    def logits(eng, s, k):
+        return eng.read_logits(B.PARD_DRAFT, k, seq=s), eng.read_logits(B.PARD_TARGET, k + 1, seq=s)
+
+    one, many = (B.Engine(t_spec, d_spec, vocab - 1, max_ctx=160, max_k=24, max_batch=7) for _ in range(2))
+    try:
+        for n, k in ((2, 8), (4, 8), (7, 4)):
+            say(f"[gpu] {pair}: {n} slots together and alone, K={k}")
+            for s in range(n):
+                assert one.prefill(prompts[s], seq=s) == many.prefill(prompts[s], seq=s)
+            for step in range(2):
+                toks, _ = many.generate_batch(list(range(n)), k, 40, max_steps=1)
+                for s in range(n):
+                    alone, _ = one.generate_batch([s], k, 40, max_steps=1)
+                    assert list(alone[0]) == list(toks[s]), f"{n} slots, step {step}, slot {s}: tokens"
+                    for got, ref, what in zip(logits(many, s, k), logits(one, s, k), ("draft", "verify")):
+                        assert np.array_equal(got, ref), f"{n} slots, step {step}, slot {s}: {what} logits"
+        cand = [int(x) for x in pi.gen_prompt(82, vocab, 24)]
+        one.verify(cand, seq=0)               # the same state in both engines
+        many.verify(cand[:8], seq=0)
+        assert np.array_equal(one.read_logits(B.PARD_TARGET, 25, seq=0)[:9], many.read_logits(B.PARD_TARGET, 9, seq=0))
+    finally:
+        one.close()
+        many.close()

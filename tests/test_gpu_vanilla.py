@@ -4,7 +4,8 @@ verify pass, on the same kernels (pard_generate_ex, PARD_MODE_VANILLA).
 
 * draft == target: every candidate is the target's greedy token, so a = K on
   every step (the one-row draft passes and the K+1-row verify pass compute the
-  same logits: the arithmetic does not depend on the pass's row count);
+  same logits: up to 64 rows the arithmetic does not depend on the pass's row
+  count);
 * lossless: the output equals the target's greedy decoding (eq. 2), for one
   slot and for a batch of slots;
 * the fused loop equals the same steps run through the granular calls
