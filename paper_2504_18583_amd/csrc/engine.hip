@@ -861,15 +861,13 @@ pard_status stage_ids(pard_ctx* c, const int* tokens, int n, const int** out) {
 }
 
 // One model's passes over n tokens (ids; d_ids: the same on the device) at
-// positions pos0.. of one slot, in chunks of pass_rows rows or, where several
-// are needed, as even ones (so none is a few rows that stream all weights).
+// positions pos0.. of one slot, in even chunks of at most pass_rows rows.
 // lm: the last chunk's last row goes through the lm_head and sets the slot's
 // first token.
 pard_status prefill_passes(pard_ctx* c, int w, int seq, const int* ids, const int* d_ids, int n, int pos0, bool lm) {
-  const int n_chunks = ceil_div(n, c->pass_rows);
-  const int per = std::min(c->pass_rows, ceil_div(ceil_div(n, n_chunks), 128) * 128);
-  for (int off = 0; off < n; off += per) {
-    const int rows = std::min(per, n - off);
+  const int n_chunks = prefill_chunks(n, c->pass_rows);
+  for (int i = 0; i < n_chunks; ++i) {
+    const int off = prefill_chunk_begin(n, n_chunks, i), rows = prefill_chunk_begin(n, n_chunks, i + 1) - off;
     FwdDesc d{};
     PassSpec ps;
     if (rows > kMaxRows) {

@@ -22,6 +22,16 @@ constexpr int kLmStrips = 8;   // strips per lm_head workgroup at up to 48 lm ro
 
 inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
+// Prefill of n rows in passes of at most pass_rows (a multiple of 128, at least
+// 512): as few passes as that takes, of even lengths in units of 128 rows, so
+// that none is a few rows that stream all weights (with two passes or more the
+// shortest has over 128).  The first row of pass i of n_chunks; i = n_chunks: n.
+inline int prefill_chunks(int n, int pass_rows) { return ceil_div(n, pass_rows); }
+inline int prefill_chunk_begin(int n, int n_chunks, int i) {
+  const long long units = ceil_div(n, 128);
+  return (int)std::min<long long>(n, (units * i + n_chunks - 1) / n_chunks * 128);
+}
+
 // The (epilogue, row tiles, strips) that k_gemm is compiled for: launch_gemm
 // instantiates these and nothing else, and a plan may name no other.
 constexpr bool gemm_instance(int epi, int mt, int S) {

@@ -1,4 +1,5 @@
-"""Every tile plan of the skinny GEMM names a kernel that exists: the planner
+"""Host-side plans.  Every tile plan of the skinny GEMM names a kernel that
+exists, and prefill chunks are even: the planner
 (csrc/gemm_plan.h, plain C++) is compiled for the host and walked over weight
 shapes and row tiles; launch_gemm instantiates exactly the (epilogue, row tiles,
 strips) of gemm_instance and refuses what gemm_launchable does."""
@@ -29,8 +30,28 @@ static int check(const char* name, int epi, const GemmPlan& p, int mt) {
   return 1;
 }
 
+// Prefill chunks of n rows: the whole prompt in order, none longer than
+// pass_rows, whole units of 128 rows but the last, none of a few rows.
+static int check_chunks(int n, int pass_rows) {
+  const int m = prefill_chunks(n, pass_rows);
+  int at = 0, bad = m != ceil_div(n, pass_rows);
+  for (int i = 0; i < m; ++i) {
+    const int b = prefill_chunk_begin(n, m, i), e = prefill_chunk_begin(n, m, i + 1);
+    bad |= b != at || b % 128 != 0 || e <= b || e - b > pass_rows || (m > 1 && e - b <= 128);
+    at = e;
+  }
+  bad |= at != n;
+  if (bad) printf("chunks: %d rows in passes of %d\n", n, pass_rows);
+  return bad;
+}
+
 int main() {
   int bad = 0;
+  for (int pass_rows = 512; pass_rows <= 4096; pass_rows += 256) {
+    for (int n = 1; n <= 40000; ++n) bad += check_chunks(n, pass_rows);
+    for (int n = 126900; n <= 127100; ++n) bad += check_chunks(n, pass_rows);
+    for (int n = (1 << 24) - 400; n <= (1 << 24); n += 7) bad += check_chunks(n, pass_rows);
+  }
   const int kbs[] = {1, 2, 3, 4, 7, 8, 28, 64, 128, 255, 256, 383, 384, 448, 592, 1000, 2048};
   for (int mt = 1; mt <= 4; ++mt)
     for (int kb : kbs) {
@@ -52,12 +73,12 @@ int main() {
 
 
 @pytest.mark.skipif(shutil.which("g++") is None, reason="needs a host C++ compiler")
-def test_every_plan_has_its_kernel(tmp_path):
+def test_every_plan_has_its_kernel_and_chunks_are_even(tmp_path):
     src, exe = tmp_path / "plans.cpp", tmp_path / "plans"
     src.write_text(PROGRAM)
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, str(src), "-o", str(exe)], check=True)
     res = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
-    assert res.returncode == 0, f"plans without a kernel:\n{res.stdout[:2000]}"
+    assert res.returncode == 0, f"wrong plans:\n{res.stdout[:2000]}"
 
 
 class _RowsPlan(ctypes.Structure):
