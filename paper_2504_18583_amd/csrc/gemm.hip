@@ -1338,6 +1338,8 @@ __global__ __launch_bounds__(1024) void k_lm_tail(const TailArgs p) {
   if (clock && part == 0 && tid == 0) clock_tail_start(p);
   const PassSeq ps = dp->seq[sj];
   const int rows = min(ps.lm_rows, kMaxK + 1);
+  const bool sampling =
+      p.samp_k > 0.f && (p.tail == TAIL_PREFILL || p.tail == TAIL_DRAFT || p.tail == TAIL_VERIFY);
   for (int r = wave; r < rows; r += 16) {
     float bv = -INFINITY;
     int bi = INT_MAX;
@@ -1357,15 +1359,15 @@ __global__ __launch_bounds__(1024) void k_lm_tail(const TailArgs p) {
         if (better(xv[u], xi[u], bv, bi)) { bv = xv[u]; bi = xi[u]; }
     }
     wave_best(bv, bi);
+    const float S = sampling ? row_sum(p, ps.lm0 + r, bv, lane) : 0.f;
     if (lane == 0) {
       res_s[r] = (bi >= 0 && bi < p.vocab) ? bi : 0;
       Ms[r] = bv;
+      Ss[r] = S;
     }
   }
-  const bool sampling =
-      p.samp_k > 0.f && (p.tail == TAIL_PREFILL || p.tail == TAIL_DRAFT || p.tail == TAIL_VERIFY);
+  __syncthreads();
   if (!sampling) {
-    __syncthreads();
     if (tid == 0) {
       for (int r = 0; r < rows; ++r) p.result[ps.lm0 + r] = res_s[r];
       p.lm_map[ps.slot] = int2{ps.lm0, rows};
@@ -1380,11 +1382,6 @@ __global__ __launch_bounds__(1024) void k_lm_tail(const TailArgs p) {
     __shared__ int pick_s[2], a_s, tok_s, last_s;
     SeqState* st = p.states + ps.slot;
     const int draw = st->draw;
-    for (int r = wave; r < rows; r += 16) {          // (the wavefront that found the row's maximum)
-      const float S = row_sum(p, ps.lm0 + r, Ms[r], lane);
-      if (lane == 0) Ss[r] = S;
-    }
-    __syncthreads();
     if (p.tail == TAIL_DRAFT || p.tail == TAIL_PREFILL) {
       const int purpose = p.tail == TAIL_PREFILL ? PURPOSE_FIRST : PURPOSE_DRAFT;
       for (int r = wave; r < rows; r += 16) {
