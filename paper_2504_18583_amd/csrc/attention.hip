@@ -512,10 +512,11 @@ __global__ __launch_bounds__(256) void k_attn_merge(const AttnArgs p) {
 
 template <int HD, int NQ>
 hipError_t launch_hd_nq(const AttnArgs& a, hipStream_t st) {
-  if (a.wide) {                      // one chunk, 8 waves: no merge kernel
-    k_attn<HD, NQ, 2 * kAttnWaves><<<dim3(a.n_kv, a.n_qblocks, a.n_seq), dim3(128 * kAttnWaves), 0, st>>>(a);
-    return hipGetLastError();
-  }
+  if constexpr (NQ == 1)
+    if (a.wide) {                    // one chunk, 8 waves: no merge kernel
+      k_attn<HD, 1, 2 * kAttnWaves><<<dim3(a.n_kv, a.n_qblocks, a.n_seq), dim3(128 * kAttnWaves), 0, st>>>(a);
+      return hipGetLastError();
+    }
   // Two query tiles and more over chunks of more than two tiles a wavefront take
   // k_attn_chunk (us, 8B attention: 32 sequences of 256-2048 keys, 9 rows each,
   // 1024-key chunks 40.8 -> 36.3, 17 rows 64.0 -> 48.0; one sequence, 16384 keys,
@@ -566,7 +567,7 @@ hipError_t launch_attention(int head_dim, const AttnArgs& a, hipStream_t st) {
   if (a.split_len % 128 || a.split_len <= 0) return hipErrorInvalidValue;
   if (a.nqt < 1 || a.nqt > attn_max_q_tiles(head_dim)) return hipErrorInvalidValue;
   if (a.n_seq < 1 || a.n_seq > kMaxPassSeqs || (size_t)a.n_seq * a.n_splits > 65535) return hipErrorInvalidValue;
-  if (a.wide && a.n_splits != 1) return hipErrorInvalidValue;
+  if (a.wide && (a.n_splits != 1 || a.nqt != 1)) return hipErrorInvalidValue;
   if (head_dim == 64) return launch_hd<64>(a, st);
   if (head_dim == 128) return launch_hd<128>(a, st);
   return hipErrorInvalidValue;

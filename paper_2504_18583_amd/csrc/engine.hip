@@ -565,7 +565,7 @@ pard_status forward(pard_ctx* c, int w, const PassSpec& ps) {
   // the 8-wave kernel within its registers; at 64 it measured fastest)
   const bool wide = !rows && l_bound <= kAttnWideMaxKeys;
   int nqt = std::min(attn_max_q_tiles(s.head_dim), ceil_div(qpairs, 16));
-  if (wide) nqt = std::min(nqt, s.head_dim == 128 ? 1 : kAttnWideQTiles64);
+  if (wide) nqt = 1;   // (head_dim 64: measured ahead of 2 and 4)
   // prefill chunks: the kernel that shares the keys among the wavefronts
   const int pre_nqt = rows && ps.n_seq == 1
                           ? attn_prefill_tiles(s.head_dim, s.n_kv_heads, qpairs, ps.max_rows, l_bound) : 0;

@@ -57,13 +57,6 @@ namespace {
 // They stay in the VALU (DPP moves, then the lane swaps): through LDS shuffles
 // they were most of a sampled step's tail.
 __device__ __forceinline__ float wave_sum(float v) { return attn::sum4g(sum16(v)); }
-__device__ __forceinline__ float wave_max(float v) {
-  v = fmaxf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, false)));
-  v = fmaxf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xF, 0xF, false)));
-  v = fmaxf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x141, 0xF, 0xF, false)));
-  v = fmaxf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x140, 0xF, 0xF, false)));
-  return attn::max4g(v);
-}
 // The best (value, index) of the wavefront, in every lane.
 __device__ __forceinline__ void wave_best(float& bv, int& bi) {
   best16(bv, bi);

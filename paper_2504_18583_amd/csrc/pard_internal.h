@@ -51,7 +51,6 @@ constexpr int kAttnChunk = 256;    // keys per attention workgroup (decode passe
 constexpr int kAttnWideMaxKeys = 2048;   // decode passes up to this context: one 8-wave workgroup covers all keys
 constexpr int kAttnLongChunkMax = 2560;   // longest key chunk (a wavefront of k_attn_chunk takes about 2 us per 128 keys)
 constexpr int kAttnDecodeWGs = 256;       // decode passes: chunks grow while the grid exceeds this
-constexpr int kAttnWideQTiles64 = 1;     // query tiles per such workgroup at head_dim 64 (measured: 1 ahead of 2 and 4)
 constexpr int kAttnRecords = 512;  // max (query group, key chunk) partial records per KV head and sequence
 
 // Position of activation element (row, k) in a k-blocked buffer with `slots`
