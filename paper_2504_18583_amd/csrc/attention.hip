@@ -517,26 +517,23 @@ hipError_t launch_hd_nq(const AttnArgs& a, hipStream_t st) {
       k_attn<HD, 1, 2 * kAttnWaves><<<dim3(a.n_kv, a.n_qblocks, a.n_seq), dim3(128 * kAttnWaves), 0, st>>>(a);
       return hipGetLastError();
     }
-  // Two query tiles and more over chunks of more than two tiles a wavefront take
-  // k_attn_chunk (us, 8B attention: 32 sequences of 256-2048 keys, 9 rows each,
-  // 1024-key chunks 40.8 -> 36.3, 17 rows 64.0 -> 48.0; one sequence, 16384 keys,
-  // 640-key chunks 22.3 -> 21.4); shorter chunks, whose two tiles k_attn requests
-  // at once, and one query tile, where two of its wavefronts fit a SIMD, do not
-  // (4000 keys, 256-key chunks 13.3 against 14.9; 32 sequences, one row 26.3
-  // against 26.8).
+  // Chunks of more than two tiles a wavefront take k_attn_chunk (us, 8B
+  // attention: 32 sequences of 256-2048 keys, 9 rows each, 1024-key chunks 40.8
+  // -> 36.3, 17 rows 64.0 -> 48.0; one sequence, 16384 keys, 640-key chunks 22.3
+  // -> 21.4); shorter ones, whose two tiles k_attn requests at once, do not (4000
+  // keys, 256-key chunks 13.3 against 14.9).  With one query tile, where two of
+  // k_attn's wavefronts fit a SIMD, there is little between them (32 sequences,
+  // one row 26.3 against 26.8), and the kernel, whose sums round differently,
+  // must not depend on the pass's row count.
   const dim3 grid(a.n_kv, a.n_qblocks, a.n_seq * a.n_splits);
-  if constexpr (NQ >= 2) {
-    // Whole contexts at head_dim 64 (a workgroup per CU or fewer, whose tiles are
-    // half as long) run eight wavefronts: 32 sequences of 256-2048 keys in a
-    // model's step 31 -> 26 us; at head_dim 128 44 with either, and key chunks
-    // are slower (16384 keys 22 -> 24).
-    if (HD == 64 && a.split_len > kAttnChunk && a.n_splits == 1)
-      k_attn_chunk<HD, NQ, HD == 64 ? 8 : 4><<<grid, dim3(512), 0, st>>>(a);
-    else if (a.split_len > kAttnChunk) k_attn_chunk<HD, NQ, 4><<<grid, dim3(256), 0, st>>>(a);
-    else k_attn<HD, NQ, kAttnWaves><<<grid, dim3(64 * kAttnWaves), 0, st>>>(a);
-  } else {
-    k_attn<HD, NQ, kAttnWaves><<<grid, dim3(64 * kAttnWaves), 0, st>>>(a);
-  }
+  // Whole contexts at head_dim 64 (a workgroup per CU or fewer, whose tiles are
+  // half as long) run eight wavefronts: 32 sequences of 256-2048 keys in a
+  // model's step 31 -> 26 us; at head_dim 128 44 with either, and key chunks
+  // are slower (16384 keys 22 -> 24).
+  if (HD == 64 && a.split_len > kAttnChunk && a.n_splits == 1)
+    k_attn_chunk<HD, NQ, HD == 64 ? 8 : 4><<<grid, dim3(512), 0, st>>>(a);
+  else if (a.split_len > kAttnChunk) k_attn_chunk<HD, NQ, 4><<<grid, dim3(256), 0, st>>>(a);
+  else k_attn<HD, NQ, kAttnWaves><<<grid, dim3(64 * kAttnWaves), 0, st>>>(a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.n_splits == 1) return e;
   if (a.n_splits <= kMergeFewChunks)

@@ -344,3 +344,30 @@ def test_longest_cache_lockstep(B, n):
         say(f"    max |logit err| {ls.worst:.3g}")
     finally:
         eng.close()
+
+
+@pytest.mark.parametrize("heads,kv,hd,n", [
+    (32, 8, 128, 9000),    # chunks of 384 keys: 4 pairs of one row, 36 of nine
+    (16, 8, 64, 9000),
+    (8, 8, 128, 9000),     # no grouping
+    (16, 8, 128, 3000),    # chunks of 256 keys
+])
+def test_long_context_rows_do_not_depend_on_the_pass(B, heads, kv, hd, n):
+    """Past whole-context attention too, the root row of a one-slot verify pass
+    has bitwise the same logits alone (K = 0) and beside eight candidates, as
+    long as its pass's query pairs fit one workgroup (vanilla drafting of one
+    row against the verify pass)."""
+    wl = pi.WORKLOADS["tiny"]
+    t_spec = replace(pi.with_dtype(wl.target, "bf16"), n_layers=2, n_heads=heads, n_kv_heads=kv, head_dim=hd)
+    d_spec = replace(pi.with_dtype(wl.draft, "bf16"), n_layers=1)
+    prompt = [int(x) for x in pi.gen_prompt(33, t_spec.vocab, n)]
+    say(f"[gpu] {heads}/{kv} heads of {hd}, {n} keys: one row and nine")
+    eng, one = (B.Engine(t_spec, d_spec, wl.mask_id, max_ctx=n + 64, max_k=8) for _ in range(2))
+    try:
+        assert eng.prefill(prompt) == one.prefill(prompt)
+        eng.verify([int(x) for x in pi.gen_prompt(34, t_spec.vocab, 8)])
+        one.verify([])
+        assert np.array_equal(eng.read_logits(B.PARD_TARGET, 9)[0], one.read_logits(B.PARD_TARGET, 1)[0])
+    finally:
+        eng.close()
+        one.close()
