@@ -125,12 +125,17 @@ inline int pick_S(int epi, int n_strips, int mt) {
   // (us at 41 rows, rotating weight copies): gate/up 8B 1792 strips 56 at 2, 44
   // at 4, 41 at 7; 1B 1024 strips 17.9 at 2, 16.3 at 4, 23.6 at 8; Qwen2.5-7B
   // 2368 strips 65 at 2, 55 at 4, 70 at 8; QKV 8B 384 strips 21.4 at 1, 18.2 at 2,
-  // Qwen2.5-7B 288 strips 18.6 and 15.7, 1B 192 strips 9.2 and 11.8.
+  // Qwen2.5-7B 288 strips 18.6 and 15.7, 1B 192 strips 9.2 and 11.8.  Two strips
+  // where they are one round by themselves (512 strips x 64 k-blocks, 25 / 41 / 57
+  // rows: 10.2 / 11.7 / 13.5 at 2, 12.6 / 15.0 / 17.4 at 4), and with two row
+  // tiles where four would leave a second round half empty or more (25 rows, 128
+  // k-blocks: 1056 strips 32.6 at 2, 35.8 at 4; 1376 36.3, 37.5; 1536 37.6, 38.3;
+  // 1664 46.5, 38.7; at 41 rows 1376 42.1, 41.1).
   int s = 1;
   if (epi == EPI_QKV && n_strips > 256) s = 2;
   if (epi == EPI_SWIGLU) {
-    s = n_strips >= 512 ? 4 : 2;
     if (n_strips > 1024 && n_strips <= 1792 && n_strips % 7 == 0) return 7;
+    s = n_strips <= 512 || (mt == 2 && n_strips > 1024 && n_strips <= 1536) ? 2 : 4;
   }
   while (s > 1 && n_strips % s) s >>= 1;
   return s;

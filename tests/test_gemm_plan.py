@@ -52,6 +52,12 @@ int main() {
     for (int n = 126900; n <= 127100; ++n) bad += check_chunks(n, pass_rows);
     for (int n = (1 << 24) - 400; n <= (1 << 24); n += 7) bad += check_chunks(n, pass_rows);
   }
+  // gate/up of 17 to 64 rows: no wider tile than fills its rounds
+  for (int mt = 2; mt <= 4; ++mt) {
+    bad += pick_S(EPI_SWIGLU, 512, mt) != 2 || pick_S(EPI_SWIGLU, 516, mt) != 4 || pick_S(EPI_SWIGLU, 1344, mt) != 7;
+    bad += pick_S(EPI_SWIGLU, 1376, mt) != (mt == 2 ? 2 : 4) || pick_S(EPI_SWIGLU, 1664, mt) != 4;
+  }
+  if (bad) printf("gate/up tiles\n");
   const int kbs[] = {1, 2, 3, 4, 7, 8, 28, 64, 128, 255, 256, 383, 384, 448, 592, 1000, 2048};
   for (int mt = 1; mt <= 4; ++mt)
     for (int kb : kbs) {
