@@ -79,10 +79,13 @@ inline int pick_S(int epi, int n_strips, int mt) {
   // lm_head: eight strips per workgroup (four at 49 rows and more), fewer for
   // small vocabularies until the workgroups cover the CUs (41 rows, 4096-wide
   // hidden: 8016 strips 242 us at 2 per workgroup, 202 at 4, 194 at 8; 57 rows
-  // 264, 220, 228; 256 strips, 41 rows: 16.1 at 2, 13.4 at 1)
+  // 264, 220, 228; 256 strips, 41 rows: 16.1 at 2, 13.4 at 1).  Eight also where
+  // they are one round that leaves up to a quarter of the CUs out (9 rows: 1536
+  // strips 31.7 at 8, 34.3 at 4; 2000, a vocabulary of 32000, 41.9 and 43.2; 1024
+  // 27.5 and 21.7; 41 rows: 1536 39.0 and 41.8, 2000 45.1 and 45.7)
   if (epi == EPI_LOGITS) {
     int s = mt <= 3 ? kLmStrips : 4;
-    while (s > 1 && (n_strips % s || n_strips / s < 256)) s >>= 1;
+    while (s > 1 && (n_strips % s || n_strips / s < (s == kLmStrips ? 192 : 256))) s >>= 1;
     return s;
   }
   if (mt == 1) {

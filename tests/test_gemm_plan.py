@@ -58,6 +58,9 @@ int main() {
     bad += pick_S(EPI_SWIGLU, 1376, mt) != (mt == 2 ? 2 : 4) || pick_S(EPI_SWIGLU, 1664, mt) != 4;
   }
   if (bad) printf("gate/up tiles\n");
+  for (int mt = 1; mt <= 3; ++mt)   // lm_head: eight strips from 1536 on
+    bad += pick_S(EPI_LOGITS, 1536, mt) != 8 || pick_S(EPI_LOGITS, 2000, mt) != 8 || pick_S(EPI_LOGITS, 1024, mt) != 4;
+  if (bad) printf("lm_head tiles\n");
   const int kbs[] = {1, 2, 3, 4, 7, 8, 28, 64, 128, 255, 256, 383, 384, 448, 592, 1000, 2048};
   for (int mt = 1; mt <= 4; ++mt)
     for (int kb : kbs) {
