@@ -293,3 +293,31 @@ def test_rows_do_not_depend_on_the_pass(B, pair):
     finally:
         one.close()
         many.close()
+
+
+@pytest.mark.parametrize("d,heads,kv,hd,ffn,vocab", [
+    (320, 5, 1, 64, 1000, 1040),       # 20 and 28 strips, an lm_head of 65 (odd)
+    (1056, 9, 3, 128, 2740, 4112),     # 66 and 120 strips, 257 of lm_head
+    (288, 43, 43, 64, 96, 1024),       # QKV 516 strips, O 86 k-blocks over 18 strips
+    (2080, 8, 8, 64, 4096, 2064),      # 130 strips, QKV 96
+])
+def test_row_block_widths_lockstep(B, d, heads, kv, hd, ffn, vocab):
+    """Row-block GEMMs (prefill chunks and batched passes of more than 64 rows)
+    at widths that fill no tile: ragged last column tiles of every epilogue,
+    row counts that end inside a row block, split inputs."""
+    wl, t_spec, d_spec = _tiny()
+    t_spec = replace(t_spec, n_layers=2, d_model=d, n_heads=heads, n_kv_heads=kv, head_dim=hd, ffn_dim=ffn, vocab=vocab)
+    d_spec = replace(d_spec, n_layers=1, d_model=d, n_heads=heads, n_kv_heads=kv, head_dim=hd, ffn_dim=ffn, vocab=vocab)
+    lens = [65, 97, 130, 144, 145, 200, 257, 290, 330]
+    prompts = [[int(x) for x in pi.gen_prompt(91, vocab, n, b)] for b, n in enumerate(lens)]
+    target, draft = oracle.build_model(t_spec), oracle.build_model(d_spec)
+    eng = B.Engine(t_spec, d_spec, vocab - 1, max_ctx=420, max_k=8, max_batch=len(prompts))
+    try:
+        bl = BatchLockstep(eng, target, draft, prompts, 8, vocab - 1, tag=f"d{d} {heads}/{kv}x{hd} f{ffn} v{vocab}")
+        bl.prefill()
+        for step in range(2):
+            say(f"[gpu] row-block widths d{d} {heads}/{kv}x{hd} ffn {ffn} vocab {vocab}: step {step}")
+            bl.step(n_tokens=40)
+        say(f"    max |logit err| {bl.worst:.3g}")
+    finally:
+        eng.close()
