@@ -1,8 +1,8 @@
 // Grouped-query causal attention of a short block of query rows against the
 // fp16 KV cache (the draft pass with its mask rows, the verify pass, prefill
-// chunks of few rows over long contexts), on gfx950 MFMA.  Q, K, V, the probabilities and the output are
-// fp16 (10-bit mantissa: bf16 scores drift past the logit tolerance at 8B
-// width).
+// chunks of few rows over long contexts), on gfx950 MFMA.  Q, K, V, the
+// probabilities and the output are fp16 (10-bit mantissa: bf16 scores drift past
+// the logit tolerance at 8B width).
 //
 // A workgroup serves one sequence of the pass, one KV head, one group of 16*NQ
 // (row, head-in-group) query pairs -- for decode passes every pair of the KV
@@ -32,10 +32,12 @@
 // (k_attn_merge_few in chunk order for up to 16 chunks, k_attn_merge over lanes
 // for more).
 // All reductions have a fixed order, chunk boundaries sit at fixed multiples
-// of split_len and a query's arithmetic does not depend on which other pairs
-// share its workgroup: results are deterministic and a query's result does
-// not depend on the other rows of the pass.  Chunks past a query's position
-// contribute exact zeros.
+// of split_len, the kernel follows from the chunks alone and a query's
+// arithmetic does not depend on which other pairs share its workgroup: results
+// are deterministic, and a query's result depends on the other rows of the pass
+// only through the chunk length (fixed up to kAttnWideMaxKeys; past it, it
+// follows from the number of sequences and query groups).  Chunks past a query's
+// position contribute exact zeros.
 #include "attn_tile.h"
 
 namespace pard {
