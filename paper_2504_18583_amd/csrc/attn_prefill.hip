@@ -22,7 +22,11 @@
 //
 // One layer of the 8B attention (head_dim 128) at 4096 rows from position 0:
 // k_attn 648 us (212 TFLOP/s), this 154 (894); at position 4096 1070 -> 432
-// (955).  The 1B draft's (head_dim 64): 489 -> 91 (758), 771 -> 255 (808).
+// (955).  The 1B draft's (head_dim 64): 489 -> 91 (758), 771 -> 255 (808).  In the
+// trace of an 8192-token prompt (profiles/prefill_8b_kernel_trace.txt), a layer's
+// attention in 512-row chunks by k_attn with its merges 1427 us, here in two
+// 4096-row chunks 549; the draft's 869 and 351; 517 rows: 23.9 -> 12.2 and 11.9 ->
+// 8.6.
 #include "attn_tile.h"
 #include "pard_internal.h"
 

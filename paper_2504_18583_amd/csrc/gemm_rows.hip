@@ -20,10 +20,13 @@
 // the loop over whole rings has no branch (with one, every wait at the join
 // covers all LDS reads in flight).
 //
-// Against the earlier form (A through registers into a two-deep LDS buffer,
-// one 144 x 256 tile per CU; TFLOP/s): gate/up of the 8B shape, 288 rows 753 ->
-// 870, 512 rows 830 -> 870; 4096 rows, which that form could not hold, 1030-1060
-// (torch's fp16 matmul at 8192^3: 1260).
+// Against the earlier form (A through registers into a two-deep LDS buffer, one
+// 144 x 256 tile per CU), gate/up of the 8B shape in kernel traces of whole
+// calls (profiles/prefill_8b_kernel_trace.txt and the batch-32 traces): the 288
+// rows of 32 conversations' steps 92.3 -> 80.8 us (837 TFLOP/s), a 517-row prompt
+// 176 -> 141 us (862), an 8192-row prompt 170 us for each 512-row chunk, which was
+// the longest (709), -> 929 us for each 4096-row one (1036; torch's fp16 matmul
+// at 8192^3: 1150).
 //
 // Blocks are numbered so that the row blocks of one column tile run on the
 // same XCD at about the same time (the hardware deals block i to XCD i % 8):
@@ -35,8 +38,9 @@
 // Epilogues: as in the skinny GEMM.  Stores of 2 bytes straight from the
 // accumulator layout cost as much as a narrow GEMM, so QKV and the residual go
 // through a transpose within quads of lanes (8 and 16 bytes a lane) and gate/up
-// through LDS: QKV 8B at 4096 rows 272 -> 204 us, at 517 rows 54 -> 42; O 165 ->
-// 144; 1B QKV 111 -> 69.
+// through LDS (stand-alone launches at 4096 rows: QKV 8B 272 -> 204 us, O 165 ->
+// 144, 1B QKV 111 -> 69; the 8B QKV of a 517-row prompt, with its earlier split's
+// reduction, 72 -> 49 us in the traces).
 #include "attn_tile.h"
 #include "gemm_util.h"
 #include "pard_internal.h"
