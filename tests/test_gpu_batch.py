@@ -300,6 +300,7 @@ def test_rows_do_not_depend_on_the_pass(B, pair):
     (1056, 9, 3, 128, 2740, 4112),     # 66 and 120 strips, 257 of lm_head
     (288, 43, 43, 64, 96, 1024),       # QKV 516 strips, O 86 k-blocks over 18 strips
     (2080, 8, 8, 64, 4096, 2064),      # 130 strips, QKV 96
+    (64, 1, 1, 64, 32, 64),            # four strips, one and two k-blocks
 ])
 def test_row_block_widths_lockstep(B, d, heads, kv, hd, ffn, vocab):
     """Row-block GEMMs (prefill chunks and batched passes of more than 64 rows)
